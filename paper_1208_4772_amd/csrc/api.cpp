@@ -586,6 +586,25 @@ int dg_mesh_setup(const dg_mesh_desc *d, void *stream, dg_mesh **out) {
         SETUP_TRY(hipStreamSynchronize(st));
     }
     if (dm.av) {
+        // operator fragments of the gradient kernel
+        const size_t nG = grad_opsG_values(P);
+        if (dm.fp32) {
+            float *opsG_d;
+            if ((rc = m->alloc(&opsG_d, nG))) return cleanup(rc);
+            std::vector<float> h(nG);
+            grad_fill_opsG(P, ref.Dr.data(), ref.Ds.data(), ref.LIFT.data(), h.data());
+            SETUP_TRY(hipMemcpyAsync(opsG_d, h.data(), sizeof(float) * nG, hipMemcpyHostToDevice, st));
+            SETUP_TRY(hipStreamSynchronize(st));
+            dm.opsG = opsG_d;
+        } else {
+            double *opsG_d;
+            if ((rc = m->alloc(&opsG_d, nG))) return cleanup(rc);
+            std::vector<double> h(nG);
+            grad_fill_opsG64(P, ref.Dr.data(), ref.Ds.data(), ref.LIFT.data(), h.data());
+            SETUP_TRY(hipMemcpyAsync(opsG_d, h.data(), sizeof(double) * nG, hipMemcpyHostToDevice, st));
+            SETUP_TRY(hipStreamSynchronize(st));
+            dm.opsG64 = opsG_d;
+        }
         char *rs;
         const size_t rbytes = align256(size_t(K) * m->elem_bytes) + 2 * m->state_bytes();
         if ((rc = m->alloc(&rs, rbytes))) return cleanup(rc);
@@ -646,9 +665,9 @@ int dg_rhs(dg_mesh *m, const void *U, void *rhs, double t, void *stream) {
         void *Q = base + align256(size_t(m->dm.K) * m->elem_bytes);
         HIP_TRY(launch_sensor(m->dm, U, eps, st));
         HIP_TRY(launch_avgrad(m->dm, U, eps, Q, st));
-        HIP_TRY(launch_stage(m->dm, U, nullptr, nullptr, rhs, 0, eps, Q, st));
+        HIP_TRY(launch_stage(m->dm, U, nullptr, nullptr, rhs, 0, Q, st));
     } else {
-        HIP_TRY(launch_stage(m->dm, U, nullptr, nullptr, rhs, 0, nullptr, nullptr, st));
+        HIP_TRY(launch_stage(m->dm, U, nullptr, nullptr, rhs, 0, nullptr, st));
     }
     m->mark(st);
     return DG_OK;
@@ -715,7 +734,7 @@ static int step_impl(dg_mesh *m, void *U, void *work, double dt, hipStream_t st,
                 HIP_TRY(launch_avgrad(m->dm, in[s], eps, Q, st));
             }
             HIP_TRY(m->time_begin(st));
-            HIP_TRY(launch_stage_mfma(m->dm, in[s], out[s], R, nullptr, s, ms, st, eps, Q));
+            HIP_TRY(launch_stage_mfma(m->dm, in[s], out[s], R, nullptr, s, ms, st, Q));
             HIP_TRY(m->time_end(st));
         }
         return DG_OK;
@@ -729,7 +748,7 @@ static int step_impl(dg_mesh *m, void *U, void *work, double dt, hipStream_t st,
             if (int rc = av_prepare(m, in[s], w, st)) return rc;
         }
         HIP_TRY(m->time_begin(st));
-        HIP_TRY(launch_stage(m->dm, in[s], out[s], R, nullptr, s, eps, Q, st));
+        HIP_TRY(launch_stage(m->dm, in[s], out[s], R, nullptr, s, Q, st));
         HIP_TRY(m->time_end(st));
     }
     return DG_OK;
@@ -902,8 +921,7 @@ int dg_run(dg_mesh *m, void *U, void *work, int nsteps, dg_run_stats *stats, voi
     if (m->dm.av) {
         if (int rc = av_prepare(m, U, w, st)) return rc;
     }
-    HIP_TRY(launch_stage(m->dm, U, nullptr, nullptr, scratch, 0, m->dm.av ? w + m->off_eps() : nullptr,
-                         m->dm.av ? w + m->off_Q() : nullptr, st));
+    HIP_TRY(launch_stage(m->dm, U, nullptr, nullptr, scratch, 0, m->dm.av ? w + m->off_Q() : nullptr, st));
     HIP_TRY(launch_residual(m->dm, scratch, st));
     double scal[S_NSCAL];
     int flag = 0;
@@ -956,8 +974,7 @@ int dg_residual(dg_mesh *m, const void *U, void *work, double out[4], void *stre
     if (m->dm.av) {
         if (int rc = av_prepare(m, U, w, st)) return rc;
     }
-    HIP_TRY(launch_stage(m->dm, U, nullptr, nullptr, scratch, 0, m->dm.av ? w + m->off_eps() : nullptr,
-                         m->dm.av ? w + m->off_Q() : nullptr, st));
+    HIP_TRY(launch_stage(m->dm, U, nullptr, nullptr, scratch, 0, m->dm.av ? w + m->off_Q() : nullptr, st));
     HIP_TRY(launch_residual(m->dm, scratch, st));
     HIP_TRY(hipMemcpyAsync(out, m->dm.scal + S_RES, sizeof(double) * 4, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
@@ -1037,10 +1054,10 @@ int dg_autotune(dg_mesh *m, const void *U, void *work, void *stream, int *waves_
     // (ms per launch)
     auto time_one = [&](int c, int reps, float *ms_per) -> hipError_t {
         m->dm.waves_per_block = c;
-        hipError_t e = launch_stage_mfma(m->dm, in5[0], out5[0], R, nullptr, 0, MfmaStep(), st, eps, Q);
+        hipError_t e = launch_stage_mfma(m->dm, in5[0], out5[0], R, nullptr, 0, MfmaStep(), st, Q);
         if (e == hipSuccess) e = hipEventRecord(e0, st);
         for (int r = 0; r < reps && e == hipSuccess; ++r)
-            e = launch_stage_mfma(m->dm, in5[r % 5], out5[r % 5], R, nullptr, r % 5, MfmaStep(), st, eps, Q);
+            e = launch_stage_mfma(m->dm, in5[r % 5], out5[r % 5], R, nullptr, r % 5, MfmaStep(), st, Q);
         if (e == hipSuccess) e = hipEventRecord(e1, st);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.f;
@@ -1253,10 +1270,12 @@ struct Group {
     size_t items_cap = 0;          // entries (int2)
     void *eitems = nullptr;        // viscous: (job, block of 256 elements) for the per-element sensor
     size_t eitems_cap = 0;
-    void *aitems = nullptr;        // viscous: (job, tile) of the gradient and per-node sensor
+    void *aitems = nullptr;        // viscous: (job, tile) of the per-node sensor
     size_t aitems_cap = 0;
-    int *counts = nullptr;         // device [3]: items, eitems, aitems
-    int nitems = 0, neitems = 0, naitems = 0;
+    void *gitems = nullptr;        // viscous: (job, tile) of the gradient
+    size_t gitems_cap = 0;
+    int *counts = nullptr;         // device [4]: items, eitems, aitems, gitems
+    int nitems = 0, neitems = 0, naitems = 0, ngitems = 0;
 };
 
 }  // namespace
@@ -1288,6 +1307,7 @@ struct dg_batch {
             if (g.items) (void)hipFree(g.items);
             if (g.eitems) (void)hipFree(g.eitems);
             if (g.aitems) (void)hipFree(g.aitems);
+            if (g.gitems) (void)hipFree(g.gitems);
             if (g.counts) (void)hipFree(g.counts);
         }
     }
@@ -1329,7 +1349,7 @@ int rebuild(dg_batch *b, hipStream_t st) {
             ng.waves = tw ? tw : mfma_default_waves();
             if (hipMalloc(&ng.jobs, 2 * 5 * max_jobs * mfma_args_bytes()) != hipSuccess ||
                 (av && hipMalloc(&ng.avjobs, 2 * 5 * max_jobs * av_args_bytes()) != hipSuccess) ||
-                hipMalloc(reinterpret_cast<void **>(&ng.counts), 3 * sizeof(int)) != hipSuccess) {
+                hipMalloc(reinterpret_cast<void **>(&ng.counts), 4 * sizeof(int)) != hipSuccess) {
                 if (ng.jobs) (void)hipFree(ng.jobs);
                 if (ng.avjobs) (void)hipFree(ng.avjobs);
                 return fail(DG_ENOMEM, "batch table allocation failed");
@@ -1348,7 +1368,7 @@ int rebuild(dg_batch *b, hipStream_t st) {
         const size_t nj = g.slots.size();
         const size_t rec = mfma_args_bytes(), arec = av_args_bytes();
         std::vector<char> jobs(2 * 5 * max_jobs * rec, 0), avjobs(g.av ? 2 * 5 * max_jobs * arec : 0, 0);
-        std::vector<int> items, eitems, aitems;
+        std::vector<int> items, eitems, aitems, gitems;
         for (size_t j = 0; j < nj; ++j) {
             Slot &s = b->slots[g.slots[j]];
             dg_mesh *m = s.mesh;
@@ -1375,7 +1395,7 @@ int rebuild(dg_batch *b, hipStream_t st) {
                         ms.vmax_out = vout;
                     }
                     mfma_fill_args(m->dm, in[st5], out[st5], R, st5, ms, g.waves,
-                                   jobs.data() + ((ps * 5 + st5) * max_jobs + j) * rec, eps, Q);
+                                   jobs.data() + ((ps * 5 + st5) * max_jobs + j) * rec, Q);
                     if (g.av)
                         av_fill_args(m->dm, in[st5], eps, Q, st5 == 0 ? vin : nullptr,
                                      avjobs.data() + ((ps * 5 + st5) * max_jobs + j) * arec);
@@ -1397,11 +1417,17 @@ int rebuild(dg_batch *b, hipStream_t st) {
                     aitems.push_back(int(j));
                     aitems.push_back(tt);
                 }
+                const int ng = grad_tiles(m->dm);
+                for (int tt = 0; tt < ng; ++tt) {
+                    gitems.push_back(int(j));
+                    gitems.push_back(tt);
+                }
             }
         }
         g.nitems = int(items.size() / 2);
         g.neitems = int(eitems.size() / 2);
         g.naitems = int(aitems.size() / 2);
+        g.ngitems = int(gitems.size() / 2);
         // work lists grow by doubling; a new table means a new address, so
         // the captured graph is stale
         auto grow = [&](void **p, size_t *cap, size_t need) -> int {
@@ -1420,6 +1446,7 @@ int rebuild(dg_batch *b, hipStream_t st) {
         if (g.av) {
             if (int rc = grow(&g.eitems, &g.eitems_cap, size_t(g.neitems))) return rc;
             if (int rc = grow(&g.aitems, &g.aitems_cap, size_t(g.naitems))) return rc;
+            if (int rc = grow(&g.gitems, &g.gitems_cap, size_t(g.ngitems))) return rc;
         }
         HIP_TRY(hipMemcpyAsync(g.jobs, jobs.data(), jobs.size(), hipMemcpyHostToDevice, st));
         if (g.av) HIP_TRY(hipMemcpyAsync(g.avjobs, avjobs.data(), avjobs.size(), hipMemcpyHostToDevice, st));
@@ -1429,7 +1456,9 @@ int rebuild(dg_batch *b, hipStream_t st) {
             HIP_TRY(hipMemcpyAsync(g.eitems, eitems.data(), eitems.size() * sizeof(int), hipMemcpyHostToDevice, st));
         if (!aitems.empty())
             HIP_TRY(hipMemcpyAsync(g.aitems, aitems.data(), aitems.size() * sizeof(int), hipMemcpyHostToDevice, st));
-        const int counts[3] = {g.nitems, g.neitems, g.naitems};
+        if (!gitems.empty())
+            HIP_TRY(hipMemcpyAsync(g.gitems, gitems.data(), gitems.size() * sizeof(int), hipMemcpyHostToDevice, st));
+        const int counts[4] = {g.nitems, g.neitems, g.naitems, g.ngitems};
         HIP_TRY(hipMemcpyAsync(g.counts, counts, sizeof(counts), hipMemcpyHostToDevice, st));
         // the host buffers go out of scope: wait for the copies
         HIP_TRY(hipStreamSynchronize(st));
@@ -1463,7 +1492,8 @@ int batch_step(dg_batch *b, int ps, hipStream_t st) {
             if (g.av) {
                 const char *avjobs = static_cast<const char *>(g.avjobs) + (ps * 5 + s5) * nj * arec;
                 HIP_TRY(launch_av_batch(g.P, s5 == 0, avjobs, g.aitems, g.counts + 2, int(g.aitems_cap), g.eitems,
-                                        g.counts + 1, int(g.eitems_cap), st));
+                                        g.counts + 1, int(g.eitems_cap), g.gitems, g.counts + 3, int(g.gitems_cap),
+                                        st));
             }
             const char *jobs = static_cast<const char *>(g.jobs) + (ps * 5 + s5) * nj * rec;
             HIP_TRY(launch_stage_mfma_batch(g.P, g.bf3, g.av, g.waves, jobs, g.items, g.counts, int(g.items_cap),

@@ -38,8 +38,7 @@ struct StageArgs {
     const T *__restrict__ fgeo;
     const T *__restrict__ ops;
     const double *__restrict__ dt;
-    const T *__restrict__ eps;
-    const T *__restrict__ Q;
+    const T *__restrict__ Q;   // [K][Np][8] sigma Q (viscous handles)
 };
 
 // Lane -> (local element, node) map shared by all element-tiled kernels.
@@ -103,7 +102,6 @@ __global__ __launch_bounds__(kBlock) void k_stage(StageArgs<T> a) {
     const int i = t.i, el = t.el;
 
     T u[kFields] = {};
-    T sig = T(0);
     if (t.act) {
 #pragma unroll
         for (int c = 0; c < kFields; ++c) u[c] = a.Uin[(k * kFields + c) * Np + i];
@@ -113,11 +111,10 @@ __global__ __launch_bounds__(kBlock) void k_stage(StageArgs<T> a) {
         T F[kFields] = {u[1], u[1] * vx + p, u[2] * vx, (u[3] + p) * vx};
         T G[kFields] = {u[2], u[1] * vy, u[2] * vy + p, (u[3] + p) * vy};
         if (AV) {
-            sig = sqrt(a.eps[k]);
 #pragma unroll
             for (int c = 0; c < kFields; ++c) {
-                F[c] -= sig * a.Q[((k * 2 + 0) * kFields + c) * Np + i];
-                G[c] -= sig * a.Q[((k * 2 + 1) * kFields + c) * Np + i];
+                F[c] -= a.Q[(k * Np + i) * 8 + c];
+                G[c] -= a.Q[(k * Np + i) * 8 + 4 + c];
             }
         }
 #pragma unroll
@@ -160,14 +157,11 @@ __global__ __launch_bounds__(kBlock) void k_stage(StageArgs<T> a) {
                 T vmv[kFields], vj[kFields];
 #pragma unroll
                 for (int c = 0; c < kFields; ++c)
-                    vmv[c] = sig * (nx * a.Q[((k * 2 + 0) * kFields + c) * Np + vm] +
-                                    ny * a.Q[((k * 2 + 1) * kFields + c) * Np + vm]);
+                    vmv[c] = nx * a.Q[(k * Np + vm) * 8 + c] + ny * a.Q[(k * Np + vm) * 8 + 4 + c];
                 if (kn >= 0) {
-                    const T sp = sqrt(a.eps[kn]);
 #pragma unroll
                     for (int c = 0; c < kFields; ++c) {
-                        T vpv = sp * (nx * a.Q[((kn * 2 + 0) * kFields + c) * Np + vp] +
-                                      ny * a.Q[((kn * 2 + 1) * kFields + c) * Np + vp]);
+                        T vpv = nx * a.Q[(kn * Np + vp) * 8 + c] + ny * a.Q[(kn * Np + vp) * 8 + 4 + c];
                         vj[c] = T(0.5) * (vmv[c] + vpv) - vmv[c];
                     }
                 } else {
@@ -291,6 +285,8 @@ struct AvArgs {
     const T *__restrict__ fgeo;
     const T *__restrict__ ops;
     const T *__restrict__ emax;
+    const T *__restrict__ rec;     // [K][16] geometry records (null: per-node geometry for every element)
+    const T *__restrict__ opsG;    // matrix-core fragments of Dr, Ds and LIFT
     unsigned long long *__restrict__ vmax;   // CFL-bound slots (sensor with the bound only)
     int *__restrict__ flag;                  // state check (sensor with the bound only)
 };
@@ -459,85 +455,225 @@ __global__ __launch_bounds__(kBlock) void k_sensor_elem(AvArgs<T> a) {
 // Auxiliary variable of the viscous system, q = sigma grad U (sigma =
 // sqrt eps_k), strong form with the central trace (sigma U)*:
 //   Q_x = sigma (r_x Dr U + s_x Ds U) + LIFT [Fscale n_x ((sigma U)* - sigma U-)]
+// on the matrix cores: a column is one field of one element, 16 columns (4
+// elements) a product, and Dr U, Ds U and LIFT applied to the x and y jumps
+// are four products whose rows the lane that holds them combines with the
+// metric terms (constant on a straight element, per node on a curved one, so
+// one path serves both).  Written out as sigma Q, node by node with the x
+// and y parts of the four fields adjacent ([K][Np][8]): the stage kernel
+// takes a node's or a face node's terms as two 16-byte loads.
+template <typename T, int P>
+struct GradShape {
+    static constexpr int Np = (P + 1) * (P + 2) / 2, Nfp = P + 1, NF3 = 3 * Nfp;
+    static constexpr int KSD = (Np + 3) / 4, KSL = (NF3 + 3) / 4, MT = (Np + 15) / 16;
+    static constexpr int GW = P == 1 ? 4 : (P == 2 ? 2 : 1);   // column groups per wavefront: about one task per thread
+    static constexpr int NT = kBlock / 64 * GW, EB = 4 * NT;   // column groups and elements per block
+    static constexpr int NZ = MT * (2 * KSD + KSL);            // A fragments: Dr, Ds, LIFT
+    static constexpr int NG = (NZ + 3) / 4;
+    static constexpr int SJ = 4 * KSL + 1;                     // LDS stride of a column's jumps
+    // LDS stride of a node's result: whole 16-byte vectors, spread over the banks
+    static constexpr int SQ = sizeof(T) == 4 ? 12 : 10;
+    static constexpr int RG = 32 * SJ > 4 * Np * SQ ? (32 * SJ + 3) / 4 * 4 : 4 * Np * SQ;   // of a group: jumps, then result
+    static constexpr int TPT = (EB * NF3 + kBlock - 1) / kBlock;   // face-node tasks per thread
+    static constexpr int VW = 16 / int(sizeof(T));
+    static constexpr int NV = (EB * kFields * Np / VW + kBlock - 1) / kBlock;   // 16-byte vectors per thread
+};
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+// 16-byte accesses to caller buffers, which need only be aligned to a value
+typedef float f32v16 __attribute__((ext_vector_type(4), aligned(4)));
+typedef double f64v16 __attribute__((ext_vector_type(2), aligned(8)));
+template <typename T>
+struct Vec;
+template <>
+struct Vec<float> {
+    typedef f32x4 V4;
+    typedef f32v16 V16;
+};
+template <>
+struct Vec<double> {
+    typedef f64x4 V4;
+    typedef f64v16 V16;
+};
+__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f64x4 mfma16(double a, double b, f64x4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
 template <typename T, int P>
 __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) {
-    using O = Order<P>;
-    constexpr int Np = O::Np, Nfp = O::Nfp, NF3 = O::Nface, EB = O::EB;
-    __shared__ T sU[EB][kFields][Np];
-    __shared__ T sX[EB][kFields][NF3];
-    __shared__ T sY[EB][kFields][NF3];
-    // Dr, Ds and LIFT staged once per block (the same values in the same
-    // order as from global memory, so the results do not change; the block
-    // then reads them from LDS instead of issuing a cached load per entry)
-    constexpr int NOPS = 2 * Np * Np + Np * NF3;
-    __shared__ T sOps[NOPS];
-    LdsCopy<T, NOPS> opsc;
-    opsc.load(a.ops);
-    Tile<P> t(a.K, tile);
-    const long k = t.k;
-    const int i = t.i, el = t.el;
-    T sig = 0;
-    if (t.act) {
-        sig = sqrt(a.eps_in[k]);
+    using S = GradShape<T, P>;
+    using V4 = typename Vec<T>::V4;
+    using V16 = typename Vec<T>::V16;
+    constexpr int Np = S::Np, Nfp = S::Nfp, NF3 = S::NF3, KSD = S::KSD, KSL = S::KSL, MT = S::MT, GW = S::GW;
+    constexpr int EB = S::EB, NG = S::NG, SJ = S::SJ, SQ = S::SQ, RG = S::RG, TPT = S::TPT, VW = S::VW, NV = S::NV;
+    __shared__ __attribute__((aligned(16))) T sU[EB * kFields * Np];
+    __shared__ __attribute__((aligned(16))) T sW[S::NT * RG];
+    __shared__ T sG[EB][16];
+    __shared__ T sSig[EB];
+    const long k0 = (long)tile * EB;
+    const int nel = (int)min((long)EB, (long)a.K - k0);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int nflt = nel * kFields * Np, nv = nflt / VW, ntask = nel * NF3;
+
+    // loads: connectivity, the tile and its geometry, then the neighbours'
+    // traces, which stay in flight across the first barrier (a boundary
+    // face's neighbour is the element itself)
+    int info[TPT], nb[TPT];
 #pragma unroll
-        for (int c = 0; c < kFields; ++c) sU[el][c][i] = a.U[(k * kFields + c) * Np + i];
+    for (int t = 0; t < TPT; ++t) {
+        const int task = min(tid + t * kBlock, ntask - 1);
+        const int e = task / NF3, f = (task - e * NF3) / Nfp;
+        info[t] = a.finfo[k0 + e];
+        nb[t] = a.nbr[(k0 + e) * 3 + f];
     }
-    opsc.store(sOps);
+    const T *Ut = a.U + k0 * kFields * Np;
+    V16 uv[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int z = min(tid + v * kBlock, nv - 1);
+        uv[v] = nv > 0 ? reinterpret_cast<const V16 *>(Ut)[z] : V16{};
+    }
+    for (int z = tid; z < nel * 16; z += kBlock) (&sG[0][0])[z] = a.rec ? a.rec[k0 * 16 + z] : T(1);
+    if (tid < nel) sSig[tid] = sqrt(a.eps_in[k0 + tid]);
+    T up[TPT][kFields], sp[TPT];
+#pragma unroll
+    for (int t = 0; t < TPT; ++t) {
+        const int task = min(tid + t * kBlock, ntask - 1);
+        const int q = task % NF3, f = q / Nfp, j = q - f * Nfp;
+        const int vp = face_node(P, face_nbr_face(info[t], f), Nfp - 1 - j);
+        const T *src = a.U + (long)nb[t] * kFields * Np + vp;
+#pragma unroll
+        for (int c = 0; c < kFields; ++c) up[t][c] = src[c * Np];
+        sp[t] = a.eps_in[nb[t]];
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int z = tid + v * kBlock;
+        if (z < nv) {
+#pragma unroll
+            for (int e = 0; e < VW; ++e) sU[VW * z + e] = uv[v][e];
+        }
+    }
+    for (int z = VW * nv + tid; z < nflt; z += kBlock) sU[z] = Ut[z];
     __syncthreads();
-    if (t.act) {
-        const int info = a.finfo[k];
-        for (int q = i; q < NF3; q += Np) {
-            const int f = q / Nfp, j = q - f * Nfp;
-            const int vm = face_node(P, f, j);
-            T um[kFields], up[kFields];
+
+    // jumps Fscale n ((sigma U)* - sigma U-) at the face nodes, column-major
 #pragma unroll
-            for (int c = 0; c < kFields; ++c) um[c] = sU[el][c][vm];
-            const T nx = a.fgeo[(k * 3 + 0) * NF3 + q];
-            const T ny = a.fgeo[(k * 3 + 1) * NF3 + q];
-            const T fs = a.fgeo[(k * 3 + 2) * NF3 + q];
-            const int code = face_bc(info, f);
-            T sp = sig;
-            if (code == BC_INTERIOR) {
-                const long kn = a.nbr[k * 3 + f];
-                const int vp = face_node(P, face_nbr_face(info, f), Nfp - 1 - j);
-                sp = sqrt(a.eps_in[kn]);
+    for (int t = 0; t < TPT; ++t) {
+        const int task = tid + t * kBlock;
+        if (task < ntask) {
+            const int e = task / NF3, q = task - e * NF3, f = q / Nfp;
+            const int vm = face_node(P, f, q - f * Nfp);
+            T um[kFields];
 #pragma unroll
-                for (int c = 0; c < kFields; ++c) up[c] = a.U[(kn * kFields + c) * Np + vp];
-            } else {
-                ghost_state(a.g, code, um, nx, ny, a.ff, up);
+            for (int c = 0; c < kFields; ++c) um[c] = sU[(e * kFields + c) * Np + vm];
+            T nx = sG[e][4 + 3 * f], ny = sG[e][5 + 3 * f], fs = sG[e][6 + 3 * f];
+            if (sG[e][13] != T(0)) {
+                const T *gf = a.fgeo + (k0 + e) * 3 * NF3 + q;
+                nx = gf[0];
+                ny = gf[NF3];
+                fs = gf[2 * NF3];
             }
+            const int code = face_bc(info[t], f);
+            const T sig = sSig[e];
+            T sn = sqrt(sp[t]);
+            if (code != BC_INTERIOR) {
+                ghost_state(a.g, code, um, nx, ny, a.ff, up[t]);
+                sn = sig;
+            }
+            T *J = sW + (e >> 2) * RG + (e & 3) * kFields * 2 * SJ + q;
 #pragma unroll
             for (int c = 0; c < kFields; ++c) {
-                T star = T(0.5) * (sig * um[c] + sp * up[c]);
-                T d = fs * (star - sig * um[c]);
-                sX[el][c][q] = nx * d;
-                sY[el][c][q] = ny * d;
+                const T d = fs * (T(0.5) * (sig * um[c] + sn * up[t][c]) - sig * um[c]);
+                J[2 * c * SJ] = nx * d;
+                J[(2 * c + 1) * SJ] = ny * d;
             }
         }
     }
+    V4 ga[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) ga[g] = reinterpret_cast<const V4 *>(a.opsG)[g * 64 + lane];
     __syncthreads();
-    if (!t.act) return;
-    const T rx = a.geo[(k * 4 + 0) * Np + i], sx = a.geo[(k * 4 + 1) * Np + i];
-    const T ry = a.geo[(k * 4 + 2) * Np + i], sy = a.geo[(k * 4 + 3) * Np + i];
+
+    const int col = lane & 15, kq = lane >> 4;
 #pragma unroll
-    for (int c = 0; c < kFields; ++c) {
-        T dru = 0, dsu = 0;
+    for (int gi = 0; gi < GW; ++gi) {
+        const int t = wave * GW + gi;
+        if (4 * t >= nel) break;
+        V4 ar[MT], as[MT], ax[MT], ay[MT];
 #pragma unroll
-        for (int j = 0; j < Np; ++j) {
-            const T uv = sU[el][c][j];
-            dru += sOps[i * Np + j] * uv;
-            dsu += sOps[Np * Np + i * Np + j] * uv;
+        for (int mt = 0; mt < MT; ++mt) ar[mt] = as[mt] = ax[mt] = ay[mt] = V4{T(0), T(0), T(0), T(0)};
+        // a column's operand rows beyond its length are zero (the columns of
+        // elements past the mesh's end are never written out)
+        const T *ub = sU + (t * 16 + col) * Np, *jx = sW + t * RG + col * 2 * SJ, *jy = jx + SJ;
+#pragma unroll
+        for (int ks = 0; ks < KSD; ++ks) {
+            const int row = 4 * ks + kq;
+            const T b = 4 * ks + 3 < Np || row < Np ? ub[row] : T(0);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const int z = ks * MT + mt, y = KSD * MT + z;
+                ar[mt] = mfma16(ga[z / 4][z % 4], b, ar[mt]);
+                as[mt] = mfma16(ga[y / 4][y % 4], b, as[mt]);
+            }
         }
-        T qx = sig * (rx * dru + sx * dsu);
-        T qy = sig * (ry * dru + sy * dsu);
 #pragma unroll
-        for (int q = 0; q < NF3; ++q) {
-            const T l = sOps[2 * Np * Np + i * NF3 + q];
-            qx += l * sX[el][c][q];
-            qy += l * sY[el][c][q];
+        for (int ks = 0; ks < KSL; ++ks) {
+            const int row = 4 * ks + kq;
+            const bool in = 4 * ks + 3 < NF3 || row < NF3;
+            const T bx = in ? jx[row] : T(0), by = in ? jy[row] : T(0);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const int z = 2 * KSD * MT + ks * MT + mt;
+                ax[mt] = mfma16(ga[z / 4][z % 4], bx, ax[mt]);
+                ay[mt] = mfma16(ga[z / 4][z % 4], by, ay[mt]);
+            }
         }
-        a.Q[((k * 2 + 0) * kFields + c) * Np + i] = qx;
-        a.Q[((k * 2 + 1) * kFields + c) * Np + i] = qy;
+        // the result over the group's own (consumed) jumps
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int el = t * 4 + (col >> 2), c = col & 3;
+        if (el < nel) {
+            const T sig = sSig[el];
+            const bool curved = sG[el][13] != T(0);
+            T rx = sG[el][0], sx = sG[el][1], ry = sG[el][2], sy = sG[el][3];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    // output row of accumulator slot r (consecutive rows per
+                    // 16-lane group in FP32, interleaved by 4 in FP64)
+                    const int i = sizeof(T) == 4 ? 16 * mt + 4 * kq + r : 16 * mt + kq + 4 * r;
+                    if (i < Np) {
+                        if (curved) {
+                            const T *gk = a.geo + (k0 + el) * 4 * Np + i;
+                            rx = gk[0];
+                            sx = gk[Np];
+                            ry = gk[2 * Np];
+                            sy = gk[3 * Np];
+                        }
+                        T *o = sW + t * RG + ((el & 3) * Np + i) * SQ + c;
+                        o[0] = sig * (sig * (rx * ar[mt][r] + sx * as[mt][r]) + ax[mt][r]);
+                        o[4] = sig * (sig * (ry * ar[mt][r] + sy * as[mt][r]) + ay[mt][r]);
+                    }
+                }
+        }
+    }
+    __syncthreads();
+    // coalesced copy out, one 16-byte vector per lane
+    constexpr int VN = 8 / VW;   // vectors of a node
+    T *Qt = a.Q + k0 * Np * 8;
+    for (int z = tid; z < nel * Np * VN; z += kBlock) {
+        const int node = z / VN, h = z - node * VN, e = node / Np, i = node - e * Np;
+        const T *o = sW + (e >> 2) * RG + ((e & 3) * Np + i) * SQ + h * VW;
+        V16 v;
+#pragma unroll
+        for (int x = 0; x < VW; ++x) v[x] = o[x];
+        reinterpret_cast<V16 *>(Qt)[z] = v;
     }
 }
 
@@ -969,7 +1105,7 @@ const float *tbl_emax<float>(const DevMesh &m) { return m.emax32; }
 
 template <typename T>
 hipError_t stage_t(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs, int stage,
-                   const void *eps, const void *Q, hipStream_t st) {
+                   const void *Q, hipStream_t st) {
     StageArgs<T> a;
     a.riemann = m.riemann;
     a.K = m.K;
@@ -989,7 +1125,6 @@ hipError_t stage_t(const DevMesh &m, const void *Uin, void *Uout, void *R, void 
     a.fgeo = tbl_fgeo<T>(m);
     a.ops = tbl_ops<T>(m);
     a.dt = m.scal + S_DT;
-    a.eps = static_cast<const T *>(eps);
     a.Q = static_cast<const T *>(Q);
     return with_order(m.P, [&](auto PC) {
         constexpr int P = decltype(PC)::value;
@@ -1017,6 +1152,13 @@ AvArgs<T> av_args(const DevMesh &m) {
     a.fgeo = tbl_fgeo<T>(m);
     a.ops = tbl_ops<T>(m);
     a.emax = tbl_emax<T>(m);
+    if constexpr (sizeof(T) == 4) {
+        a.rec = m.geoA;
+        a.opsG = m.opsG;
+    } else {
+        a.rec = m.geoA64;
+        a.opsG = m.opsG64;
+    }
     a.vmax = nullptr;
     a.flag = m.flag;
     return a;
@@ -1074,14 +1216,14 @@ hipError_t launch_cast(const double *src, float *dst, size_t n, hipStream_t st) 
 }
 
 hipError_t launch_stage(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs, int stage,
-                        const void *eps, const void *Q, hipStream_t st) {
+                        const void *Q, hipStream_t st) {
     // the weak form: its own kernel; FP32 (with or without viscosity): the
     // matrix-core kernel; FP64: the FP64 matrix cores for a mesh of straight
     // elements without viscosity, else VALU
     if (m.weak) return launch_stage_weak(m, Uin, Uout, R, rhs, stage, st);
-    if (m.fp32) return launch_stage_mfma(m, Uin, Uout, R, rhs, stage, MfmaStep(), st, eps, Q);
+    if (m.fp32) return launch_stage_mfma(m, Uin, Uout, R, rhs, stage, MfmaStep(), st, Q);
     if (m.opsA64 && !m.av) return launch_stage_mfma64(m, Uin, Uout, R, rhs, stage, false, st);
-    return stage_t<double>(m, Uin, Uout, R, rhs, stage, eps, Q, st);
+    return stage_t<double>(m, Uin, Uout, R, rhs, stage, Q, st);
 }
 
 template <typename T>
@@ -1128,10 +1270,56 @@ int sensor_elem_blocks(const DevMesh &m) { return (m.K + kBlock - 1) / kBlock; }
 
 int av_tiles(const DevMesh &m) { return nblocks_rt(m.K, m.P); }
 
+static int grad_elements(int P) { return P == 1 ? 64 : (P == 2 ? 32 : 16); }
+
+int grad_tiles(const DevMesh &m) { return (m.K + grad_elements(m.P) - 1) / grad_elements(m.P); }
+
+// Fragments of the gradient's products (Dr, Ds, LIFT): lane l of fragment
+// z = ks MT + mt of an operator holds row 16 mt + l % 16, column 4 ks + l / 16
+// (zero outside the matrix), four fragments per group.
+size_t grad_opsG_values(int P) {
+    size_t n = 0;
+    (void)with_order(P, [&](auto PC) {
+        n = size_t(GradShape<float, decltype(PC)::value>::NG) * 64 * 4;
+        return hipSuccess;
+    });
+    return n;
+}
+
+template <typename T>
+static void fill_opsG(int P, const double *Dr, const double *Ds, const double *LIFT, T *out) {
+    (void)with_order(P, [&](auto PC) {
+        using S = GradShape<T, decltype(PC)::value>;
+        static_assert(S::EB == (S::Nfp == 2 ? 64 : (S::Nfp == 3 ? 32 : 16)), "grad_elements");
+        for (int z = 0; z < S::NG * 64 * 4; ++z) out[z] = T(0);
+        const double *ops[3] = {Dr, Ds, LIFT};
+        int first = 0;
+        for (int o = 0; o < 3; ++o) {
+            const int cols = o < 2 ? S::Np : S::NF3, ksn = (cols + 3) / 4;
+            for (int z = 0; z < ksn * S::MT; ++z)
+                for (int l = 0; l < 64; ++l) {
+                    const int row = 16 * (z % S::MT) + (l & 15), c = 4 * (z / S::MT) + (l >> 4);
+                    if (row < S::Np && c < cols)
+                        out[(((first + z) / 4) * 64 + l) * 4 + (first + z) % 4] = T(ops[o][row * cols + c]);
+                }
+            first += ksn * S::MT;
+        }
+        return hipSuccess;
+    });
+}
+
+void grad_fill_opsG(int P, const double *Dr, const double *Ds, const double *LIFT, float *out) {
+    fill_opsG<float>(P, Dr, Ds, LIFT, out);
+}
+void grad_fill_opsG64(int P, const double *Dr, const double *Ds, const double *LIFT, double *out) {
+    fill_opsG<double>(P, Dr, Ds, LIFT, out);
+}
+
 hipError_t launch_av_batch(int P, bool cfl, const void *jobs, const void *items, const int *nitems_dev,
                            int capacity, const void *eitems, const int *neitems_dev, int ecapacity,
-                           hipStream_t st) {
+                           const void *gitems, const int *ngitems_dev, int gcapacity, hipStream_t st) {
     if (capacity <= 0) return hipSuccess;
+    const auto *git = static_cast<const int2 *>(gitems);
     const auto *j = static_cast<const AvArgs<float> *>(jobs);
     const auto *it = static_cast<const int2 *>(items);
     const auto *eit = static_cast<const int2 *>(eitems);
@@ -1144,7 +1332,7 @@ hipError_t launch_av_batch(int P, bool cfl, const void *jobs, const void *items,
                                neitems_dev);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_avgrad_batch<PP>), dim3(capacity), dim3(kBlock), 0, st, j, it, nitems_dev);
+        hipLaunchKernelGGL((k_avgrad_batch<PP>), dim3(gcapacity), dim3(kBlock), 0, st, j, git, ngitems_dev);
         return hipGetLastError();
     });
 }
@@ -1157,7 +1345,7 @@ static hipError_t avgrad_t(const DevMesh &m, const void *U, const void *eps, voi
     a.Q = static_cast<T *>(Q);
     return with_order(m.P, [&](auto PC) {
         constexpr int P = decltype(PC)::value;
-        hipLaunchKernelGGL((k_avgrad<T, P>), dim3(nblocks<P>(m.K)), dim3(kBlock), 0, st, a);
+        hipLaunchKernelGGL((k_avgrad<T, P>), dim3(grad_tiles(m)), dim3(kBlock), 0, st, a);
         return hipGetLastError();
     });
 }

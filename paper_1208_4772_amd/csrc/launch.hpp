@@ -64,6 +64,8 @@ struct DevMesh {
     const float *opsA = nullptr;    // MFMA A operand table
     const double *opsA64 = nullptr; // FP64 handles of straight elements without viscosity: the
                                     // FP64 matrix-core stage's A operand (null: the VALU stage)
+    const float *opsG = nullptr;    // viscous handles: fragments of the gradient's operators
+    const double *opsG64 = nullptr;
     const double *geoA64 = nullptr; // ... and its [K][16] geometry records (k_pack_affine64)
     const unsigned *opsB = nullptr; // BF16x3 A operand table (hi and lo splits)
     int Kc = 0;
@@ -111,9 +113,9 @@ hipError_t launch_cast(const double *src, float *dst, size_t n, hipStream_t st);
 
 // rhs of state U (mode 0) or one LSERK stage (mode 1):
 //   R = a_s R + dt rhs (stage 0: R = dt rhs), Uout = Uin + b_s R.
-// eps: [K] viscosities and Q: [K][2][4][Np] gradients (AV only).
+// Q: [K][Np][8] sigma Q, x parts of the four fields then y parts (AV only).
 hipError_t launch_stage(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs,
-                        int stage, const void *eps, const void *Q, hipStream_t st);
+                        int stage, const void *Q, hipStream_t st);
 // Time-step handling of one matrix-core stage launch.
 struct MfmaStep {
     int cfl_mode = 0;      // 1: first stage computes dt from *vmax_in (and books it)
@@ -124,14 +126,13 @@ struct MfmaStep {
 };
 // FP32 matrix-core stage kernel (no artificial viscosity)
 hipError_t launch_stage_mfma(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs, int stage,
-                             const MfmaStep &step, hipStream_t st, const void *eps = nullptr,
-                             const void *Q = nullptr);
+                             const MfmaStep &step, hipStream_t st, const void *Q = nullptr);
 int mfma_curved_bit();
 // batched meshes: per-(mesh, stage) argument records in device memory and a
 // work list of (record, tile) items, all meshes of order P
 size_t mfma_args_bytes();
 void mfma_fill_args(const DevMesh &m, const void *Uin, void *Uout, void *R, int stage, const MfmaStep &step,
-                    int waves, void *out, const void *eps = nullptr, const void *Q = nullptr);
+                    int waves, void *out, const void *Q = nullptr);
 int mfma_tiles(const DevMesh &m, int waves);
 int mfma_default_waves();
 // Batched launches: one work item per workgroup over a list whose length
@@ -167,7 +168,7 @@ hipError_t launch_sensor(const DevMesh &m, const void *U, void *eps, hipStream_t
 // hold zeros or smaller bounds), and the state check into *flag
 hipError_t launch_sensor_cfl(const DevMesh &m, const void *U, void *eps, unsigned long long *vmax,
                              hipStream_t st);
-// LDG auxiliary gradient Q from U and eps
+// LDG auxiliary gradient from U and eps, as sigma Q [K][Np][8]
 hipError_t launch_avgrad(const DevMesh &m, const void *U, const void *eps, void *Q, hipStream_t st);
 // batched FP32 viscous handles of order P: per-(mesh, stage) argument
 // records and the (record, tile) work list of the stage kernel's batch;
@@ -175,14 +176,19 @@ hipError_t launch_avgrad(const DevMesh &m, const void *U, const void *eps, void 
 // gradient over all of them
 size_t av_args_bytes();
 void av_fill_args(const DevMesh &m, const void *U, void *eps, void *Q, unsigned long long *vmax, void *out);
-// items: (job, tile) pairs of the viscous kernels' tiles (av_tiles per
+// items: (job, tile) pairs of the per-node sensor's tiles (av_tiles per
 // mesh); eitems: (job, block) pairs of blocks of 256 elements for the
-// per-element sensor
+// per-element sensor; gitems: the gradient's tiles (grad_tiles per mesh)
 hipError_t launch_av_batch(int P, bool cfl, const void *jobs, const void *items, const int *nitems_dev,
                            int capacity, const void *eitems, const int *neitems_dev, int ecapacity,
-                           hipStream_t st);
+                           const void *gitems, const int *ngitems_dev, int gcapacity, hipStream_t st);
 int sensor_elem_blocks(const DevMesh &m);
 int av_tiles(const DevMesh &m);
+int grad_tiles(const DevMesh &m);
+// matrix-core fragments of the gradient's operators
+size_t grad_opsG_values(int P);
+void grad_fill_opsG(int P, const double *Dr, const double *Ds, const double *LIFT, float *out);
+void grad_fill_opsG64(int P, const double *Dr, const double *Ds, const double *LIFT, double *out);
 // CFL reduction -> scal[S_DT] (dt_fixed > 0 overrides), accumulates S_T,
 // S_DTMIN/MAX, S_STEPS; raises *flag on bad states.
 hipError_t launch_cfl(const DevMesh &m, const void *U, const void *eps, double dt_fixed,

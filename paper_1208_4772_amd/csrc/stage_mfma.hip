@@ -91,8 +91,7 @@ struct MfmaArgs {
     const float *__restrict__ geoC;    // [Kc][4 Np + 9 Nfp]
     const float *__restrict__ opsA;    // [MT][KS][64] A operand in lane order
     const float *__restrict__ ops;     // Dr | Ds (row-major) for curved elements
-    const float *__restrict__ eps;     // [K] artificial viscosity (viscous handles)
-    const float *__restrict__ Q;       // [K][2][4][Np] sqrt(eps) grad U (viscous handles)
+    const f32x4 *__restrict__ Q;       // [K][Np][2] sigma Q: x, then y parts of the four fields (viscous handles)
     double *__restrict__ scal;
     const unsigned long long *__restrict__ vmax_in;
     unsigned long long *__restrict__ vmax_out;
@@ -112,7 +111,8 @@ __device__ __forceinline__ int face_node_sel(int f, int j) {
 // Fscale are per face node.
 template <int P, bool BF3, int W, bool CURVED, bool AV>
 __device__ __forceinline__ void face_task(const MfmaArgs &a, const long k0, const int el, const int q,
-                                          const float (&upn)[4], const float *sU, const float (*sG)[16],
+                                          const float (&upn)[4], const f32x4 (&qpn)[2], const float *sU,
+                                          const float (*sG)[16],
                                           const int4 cv, const int *sFN, float *sBflat) {
     using S = MShape<P, BF3, W>;
     constexpr int Np = S::Np, Nfp = S::Nfp, NF3 = S::NF3, KP = S::KP;
@@ -155,29 +155,20 @@ __device__ __forceinline__ void face_task(const MfmaArgs &a, const long k0, cons
         // mean of both sides inside, the mirror closure at a slip wall
         // (wall_visc_jump), the interior value at the far field (so no
         // contribution there)
-        if (code == BC_INTERIOR) {
-            const int j = q - f * Nfp;
-            const long km = k0 + el;
-            const long kn = f == 0 ? cv.x : (f == 1 ? cv.y : cv.z);
-            const int vp = sFN[face_nbr_face(cv.w, f) * Nfp + Nfp - 1 - j];
-            const float sm = fsqrt(a.eps[km]), sp = fsqrt(a.eps[kn]);
-            const float *Qm = a.Q + km * 8 * Np, *Qp = a.Q + kn * 8 * Np;
+        if (code != BC_FARFIELD) {
+            const f32x4 *Qm = a.Q + ((k0 + el) * Np + vm) * 2;
+            const f32x4 vmv = nx * Qm[0] + ny * Qm[1];
+            if (code == BC_INTERIOR) {
+                const f32x4 vpv = nx * qpn[0] + ny * qpn[1];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const float vmv = sm * (nx * Qm[c * Np + vm] + ny * Qm[(4 + c) * Np + vm]);
-                const float vpv = sp * (nx * Qp[c * Np + vp] + ny * Qp[(4 + c) * Np + vp]);
-                d[c] += 0.5f * (vmv + vpv) - vmv;
+                for (int c = 0; c < 4; ++c) d[c] += 0.5f * (vmv[c] + vpv[c]) - vmv[c];
+            } else {
+                const float gm[4] = {vmv[0], vmv[1], vmv[2], vmv[3]};
+                float vj[4];
+                wall_visc_jump(gm, nx, ny, vj);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) d[c] += vj[c];
             }
-        } else if (code == BC_WALL) {
-            const long km = k0 + el;
-            const float sm = fsqrt(a.eps[km]);
-            const float *Qm = a.Q + km * 8 * Np;
-            float vmv[4], vj[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) vmv[c] = sm * (nx * Qm[c * Np + vm] + ny * Qm[(4 + c) * Np + vm]);
-            wall_visc_jump(vmv, nx, ny, vj);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) d[c] += vj[c];
         }
     }
     const f32x4 jv = {fs * d[0], fs * d[1], fs * d[2], fs * d[3]};
@@ -275,6 +266,7 @@ __device__ __forceinline__ void stage_tile(const MfmaArgs &a, const int tile) {
 #pragma unroll
     for (int t = 0; t < GPT; ++t) g4[t] = a.geoA[k0 * 4 + min(tid + t * NTH, 4 * nel - 1)];
     float upn[TPT][4];
+    f32x4 qpn[AV ? TPT : 1][2];   // viscous: the neighbour's sigma Q at the face node
 #pragma unroll
     for (int t = 0; t < TPT; ++t) {
         const int task = min(tid + t * NTH, ntask - 1);
@@ -286,6 +278,11 @@ __device__ __forceinline__ void stage_tile(const MfmaArgs &a, const int tile) {
         const float *src = a.Uin + (long)kn * 4 * Np + vp;
 #pragma unroll
         for (int c = 0; c < 4; ++c) upn[t][c] = src[c * Np];
+        if constexpr (AV) {
+            const f32x4 *qn = a.Q + ((long)kn * Np + vp) * 2;
+            qpn[t][0] = qn[0];
+            qpn[t][1] = qn[1];
+        }
     }
     f32x4 r4 = {0, 0, 0, 0};
     if (a.mode && a.stage > 0) r4 = *reinterpret_cast<const f32x4 *>(a.R + base + (flat_ok ? 4 * tid : 0));
@@ -345,13 +342,13 @@ __device__ __forceinline__ void stage_tile(const MfmaArgs &a, const int tile) {
         float F[4] = {u[1], u[1] * vx + p, u[2] * vx, (u[3] + p) * vx};
         float G[4] = {u[2], u[1] * vy, u[2] * vy + p, (u[3] + p) * vy};
         if constexpr (AV) {
-            // viscous flux sigma Q (sigma = sqrt(eps) per element)
-            const float sig = fsqrt(a.eps[k0 + eln]);
-            const float *Qe = a.Q + (k0 + eln) * 8 * Np;
+            // viscous flux sigma Q
+            const f32x4 *Qe = a.Q + ((k0 + eln) * Np + in) * 2;
+            const f32x4 qx = Qe[0], qy = Qe[1];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                F[c] -= sig * Qe[c * Np + in];
-                G[c] -= sig * Qe[(4 + c) * Np + in];
+                F[c] -= qx[c];
+                G[c] -= qy[c];
             }
         }
         const int t = eln >> 2, col = (eln & 3) * 4;
@@ -384,9 +381,9 @@ __device__ __forceinline__ void stage_tile(const MfmaArgs &a, const int tile) {
         if (task < ntask) {
             const int el = task / NF3, q = task - el * NF3;
             if (any_curved)
-                face_task<P, BF3, W, true, AV>(a, k0, el, q, upn[t], sU, sG, tconn[t], sFN, &sB[0][0][0]);
+                face_task<P, BF3, W, true, AV>(a, k0, el, q, upn[t], qpn[AV ? t : 0], sU, sG, tconn[t], sFN, &sB[0][0][0]);
             else
-                face_task<P, BF3, W, false, AV>(a, k0, el, q, upn[t], sU, sG, tconn[t], sFN, &sB[0][0][0]);
+                face_task<P, BF3, W, false, AV>(a, k0, el, q, upn[t], qpn[AV ? t : 0], sU, sG, tconn[t], sFN, &sB[0][0][0]);
         }
     }
     // the A operand of the product (the same few KB for every block, so it
@@ -813,8 +810,7 @@ int mfma_curved_bit() { return kCurvedBit; }
 int mfma_default_waves() { return kWaves; }
 
 static MfmaArgs make_args(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs, int stage,
-                          const MfmaStep &step, int waves, const void *eps = nullptr,
-                          const void *Q = nullptr) {
+                          const MfmaStep &step, int waves, const void *Q = nullptr) {
     MfmaArgs a;
     a.K = m.K;
     a.riemann = m.riemann;
@@ -840,8 +836,7 @@ static MfmaArgs make_args(const DevMesh &m, const void *Uin, void *Uout, void *R
     a.geoC = m.geoC;
     a.opsA = m.bf3 ? reinterpret_cast<const float *>(m.opsB) : m.opsA;
     a.ops = m.ops32;
-    a.eps = static_cast<const float *>(eps);
-    a.Q = static_cast<const float *>(Q);
+    a.Q = static_cast<const f32x4 *>(Q);
     a.scal = m.scal;
     a.vmax_in = step.vmax_in;
     a.vmax_out = step.vmax_out;
@@ -857,8 +852,8 @@ size_t mfma_args_bytes() { return sizeof(MfmaArgs); }
 // A batch group runs one workgroup shape (waves per workgroup) for all its
 // meshes: records and tiles are made with the group's shape.
 void mfma_fill_args(const DevMesh &m, const void *Uin, void *Uout, void *R, int stage, const MfmaStep &step,
-                    int waves, void *out, const void *eps, const void *Q) {
-    const MfmaArgs a = make_args(m, Uin, Uout, R, nullptr, stage, step, waves, eps, Q);
+                    int waves, void *out, const void *Q) {
+    const MfmaArgs a = make_args(m, Uin, Uout, R, nullptr, stage, step, waves, Q);
     std::memcpy(out, &a, sizeof(a));
 }
 
@@ -909,10 +904,10 @@ hipError_t launch_cfl_vmax_mfma(const DevMesh &m, const void *U, unsigned long l
 }
 
 hipError_t launch_stage_mfma(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs,
-                             int stage, const MfmaStep &step, hipStream_t st, const void *eps, const void *Q) {
+                             int stage, const MfmaStep &step, hipStream_t st, const void *Q) {
     const int waves = m.waves_per_block ? m.waves_per_block : default_waves(m.P);
-    if (m.av && (!eps || !Q)) return hipErrorInvalidValue;
-    MfmaArgs a = make_args(m, Uin, Uout, R, rhs, stage, step, waves, eps, Q);
+    if (m.av && !Q) return hipErrorInvalidValue;
+    MfmaArgs a = make_args(m, Uin, Uout, R, rhs, stage, step, waves, Q);
     return with_order_m(m.P, [&](auto PC) {
         constexpr int P = decltype(PC)::value;
         return with_waves(waves, [&](auto WC) {
