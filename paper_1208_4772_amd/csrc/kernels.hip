@@ -271,6 +271,7 @@ __global__ __launch_bounds__(kBlock) void k_stage(StageArgs<T> a) {
 template <typename T>
 struct AvArgs {
     int K, P;
+    int ngrad;      // blocks of the gradient
     T g;
     double gamma;   // the time-step bound is formed in FP64
     FarField<T> ff;
@@ -466,7 +467,7 @@ template <typename T, int P>
 struct GradShape {
     static constexpr int Np = (P + 1) * (P + 2) / 2, Nfp = P + 1, NF3 = 3 * Nfp;
     static constexpr int KSD = (Np + 3) / 4, KSL = (NF3 + 3) / 4, MT = (Np + 15) / 16;
-    static constexpr int GW = P == 1 ? 4 : (P == 2 ? 2 : 1);   // column groups per wavefront: about one task per thread
+    static constexpr int GW = P == 1 ? 2 : 1;                  // column groups per wavefront
     static constexpr int NT = kBlock / 64 * GW, EB = 4 * NT;   // column groups and elements per block
     static constexpr int NZ = MT * (2 * KSD + KSL);            // A fragments: Dr, Ds, LIFT
     static constexpr int NG = (NZ + 3) / 4;
@@ -512,12 +513,16 @@ __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) 
     constexpr int EB = S::EB, NG = S::NG, SJ = S::SJ, SQ = S::SQ, RG = S::RG, TPT = S::TPT, VW = S::VW, NV = S::NV;
     __shared__ __attribute__((aligned(16))) T sU[EB * kFields * Np];
     __shared__ __attribute__((aligned(16))) T sW[S::NT * RG];
-    __shared__ T sG[EB][16];
+    __shared__ __attribute__((aligned(16))) T sG[EB][16];
     __shared__ T sSig[EB];
     const long k0 = (long)tile * EB;
-    const int nel = (int)min((long)EB, (long)a.K - k0);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nflt = nel * kFields * Np, nv = nflt / VW, ntask = nel * NF3;
+    const unsigned nel = (unsigned)min((long)EB, (long)a.K - k0);
+    const unsigned tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const unsigned nflt = nel * kFields * Np, nv = nflt / VW, ntask = nel * NF3;
+    // the tile's own data through block-uniform bases and 32-bit offsets
+    const T *Ut = a.U + k0 * kFields * Np, *et = a.eps_in + k0, *rt = a.rec ? a.rec + k0 * 16 : nullptr;
+    const int *ft = a.finfo + k0, *nt = a.nbr + k0 * 3;
+    T *Qt = a.Q + k0 * Np * 8;
 
     // loads: connectivity, the tile and its geometry, then the neighbours'
     // traces, which stay in flight across the first barrier (a boundary
@@ -525,48 +530,59 @@ __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) 
     int info[TPT], nb[TPT];
 #pragma unroll
     for (int t = 0; t < TPT; ++t) {
-        const int task = min(tid + t * kBlock, ntask - 1);
-        const int e = task / NF3, f = (task - e * NF3) / Nfp;
-        info[t] = a.finfo[k0 + e];
-        nb[t] = a.nbr[(k0 + e) * 3 + f];
+        const unsigned task = min(tid + t * kBlock, ntask - 1);
+        const unsigned e = task / NF3, f = (task - e * NF3) / Nfp;
+        info[t] = ft[e];
+        nb[t] = nt[e * 3 + f];
     }
-    const T *Ut = a.U + k0 * kFields * Np;
     V16 uv[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        const int z = min(tid + v * kBlock, nv - 1);
-        uv[v] = nv > 0 ? reinterpret_cast<const V16 *>(Ut)[z] : V16{};
+    for (int v = 0; v < NV; ++v) uv[v] = reinterpret_cast<const V16 *>(Ut)[min(tid + v * kBlock, nv - 1)];
+    constexpr int NGV = (EB * 16 / VW + kBlock - 1) / kBlock;
+    V16 gv[NGV];
+#pragma unroll
+    for (int v = 0; v < NGV; ++v) {
+#pragma unroll
+        for (int e = 0; e < VW; ++e) gv[v][e] = T(1);   // no records: every element takes the per-node tables
+        if (rt) gv[v] = reinterpret_cast<const V16 *>(rt)[min(tid + v * kBlock, nel * 16 / VW - 1)];
     }
-    for (int z = tid; z < nel * 16; z += kBlock) (&sG[0][0])[z] = a.rec ? a.rec[k0 * 16 + z] : T(1);
-    if (tid < nel) sSig[tid] = sqrt(a.eps_in[k0 + tid]);
+    const T ev = et[min(tid, nel - 1)];
     T up[TPT][kFields], sp[TPT];
 #pragma unroll
     for (int t = 0; t < TPT; ++t) {
-        const int task = min(tid + t * kBlock, ntask - 1);
-        const int q = task % NF3, f = q / Nfp, j = q - f * Nfp;
+        const unsigned task = min(tid + t * kBlock, ntask - 1);
+        const unsigned q = task % NF3, f = q / Nfp, j = q - f * Nfp;
         const int vp = face_node(P, face_nbr_face(info[t], f), Nfp - 1 - j);
-        const T *src = a.U + (long)nb[t] * kFields * Np + vp;
+        const T *src = a.U + (unsigned long)(unsigned)nb[t] * (kFields * Np) + (unsigned)vp;
 #pragma unroll
         for (int c = 0; c < kFields; ++c) up[t][c] = src[c * Np];
-        sp[t] = a.eps_in[nb[t]];
+        sp[t] = a.eps_in[(unsigned)nb[t]];
     }
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const int z = tid + v * kBlock;
+        const unsigned z = tid + v * kBlock;
         if (z < nv) {
 #pragma unroll
             for (int e = 0; e < VW; ++e) sU[VW * z + e] = uv[v][e];
         }
     }
-    for (int z = VW * nv + tid; z < nflt; z += kBlock) sU[z] = Ut[z];
+#pragma unroll
+    for (int v = 0; v < NGV; ++v) {
+        const unsigned z = tid + v * kBlock;
+        if (z < nel * 16 / VW) {
+#pragma unroll
+            for (int e = 0; e < VW; ++e) (&sG[0][0])[VW * z + e] = gv[v][e];
+        }
+    }
+    if (tid < nel) sSig[tid] = sqrt(ev);
     __syncthreads();
 
     // jumps Fscale n ((sigma U)* - sigma U-) at the face nodes, column-major
 #pragma unroll
     for (int t = 0; t < TPT; ++t) {
-        const int task = tid + t * kBlock;
+        const unsigned task = tid + t * kBlock;
         if (task < ntask) {
-            const int e = task / NF3, q = task - e * NF3, f = q / Nfp;
+            const unsigned e = task / NF3, q = task - e * NF3, f = q / Nfp;
             const int vm = face_node(P, f, q - f * Nfp);
             T um[kFields];
 #pragma unroll
@@ -586,11 +602,12 @@ __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) 
                 sn = sig;
             }
             T *J = sW + (e >> 2) * RG + (e & 3) * kFields * 2 * SJ + q;
+            const T fx = fs * nx, fy = fs * ny;
 #pragma unroll
             for (int c = 0; c < kFields; ++c) {
-                const T d = fs * (T(0.5) * (sig * um[c] + sn * up[t][c]) - sig * um[c]);
-                J[2 * c * SJ] = nx * d;
-                J[(2 * c + 1) * SJ] = ny * d;
+                const T d = T(0.5) * (sig * um[c] + sn * up[t][c]) - sig * um[c];
+                J[2 * c * SJ] = fx * d;
+                J[(2 * c + 1) * SJ] = fy * d;
             }
         }
     }
@@ -599,55 +616,55 @@ __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) 
     for (int g = 0; g < NG; ++g) ga[g] = reinterpret_cast<const V4 *>(a.opsG)[g * 64 + lane];
     __syncthreads();
 
-    const int col = lane & 15, kq = lane >> 4;
+    const unsigned col = lane & 15, kq = lane >> 4;
 #pragma unroll
     for (int gi = 0; gi < GW; ++gi) {
-        const int t = wave * GW + gi;
+        const unsigned t = wave * GW + gi;
         if (4 * t >= nel) break;
+        const V4 zero = {T(0), T(0), T(0), T(0)};
         V4 ar[MT], as[MT], ax[MT], ay[MT];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) ar[mt] = as[mt] = ax[mt] = ay[mt] = V4{T(0), T(0), T(0), T(0)};
         // a column's operand rows beyond its length are zero (the columns of
         // elements past the mesh's end are never written out)
         const T *ub = sU + (t * 16 + col) * Np, *jx = sW + t * RG + col * 2 * SJ, *jy = jx + SJ;
 #pragma unroll
         for (int ks = 0; ks < KSD; ++ks) {
-            const int row = 4 * ks + kq;
+            const unsigned row = 4 * ks + kq;
             const T b = 4 * ks + 3 < Np || row < Np ? ub[row] : T(0);
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
                 const int z = ks * MT + mt, y = KSD * MT + z;
-                ar[mt] = mfma16(ga[z / 4][z % 4], b, ar[mt]);
-                as[mt] = mfma16(ga[y / 4][y % 4], b, as[mt]);
+                ar[mt] = mfma16(ga[z / 4][z % 4], b, ks ? ar[mt] : zero);
+                as[mt] = mfma16(ga[y / 4][y % 4], b, ks ? as[mt] : zero);
             }
         }
 #pragma unroll
         for (int ks = 0; ks < KSL; ++ks) {
-            const int row = 4 * ks + kq;
+            const unsigned row = 4 * ks + kq;
             const bool in = 4 * ks + 3 < NF3 || row < NF3;
             const T bx = in ? jx[row] : T(0), by = in ? jy[row] : T(0);
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
                 const int z = 2 * KSD * MT + ks * MT + mt;
-                ax[mt] = mfma16(ga[z / 4][z % 4], bx, ax[mt]);
-                ay[mt] = mfma16(ga[z / 4][z % 4], by, ay[mt]);
+                ax[mt] = mfma16(ga[z / 4][z % 4], bx, ks ? ax[mt] : zero);
+                ay[mt] = mfma16(ga[z / 4][z % 4], by, ks ? ay[mt] : zero);
             }
         }
         // the result over the group's own (consumed) jumps
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        const int el = t * 4 + (col >> 2), c = col & 3;
+        const unsigned el = t * 4 + (col >> 2), c = col & 3;
         if (el < nel) {
             const T sig = sSig[el];
             const bool curved = sG[el][13] != T(0);
             T rx = sG[el][0], sx = sG[el][1], ry = sG[el][2], sy = sG[el][3];
+            T *ob = sW + t * RG + (el & 3) * (Np * SQ) + c;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     // output row of accumulator slot r (consecutive rows per
                     // 16-lane group in FP32, interleaved by 4 in FP64)
-                    const int i = sizeof(T) == 4 ? 16 * mt + 4 * kq + r : 16 * mt + kq + 4 * r;
+                    const unsigned i = sizeof(T) == 4 ? 16 * mt + 4 * kq + r : 16 * mt + kq + 4 * r;
                     if (i < Np) {
                         if (curved) {
                             const T *gk = a.geo + (k0 + el) * 4 * Np + i;
@@ -656,7 +673,7 @@ __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) 
                             ry = gk[2 * Np];
                             sy = gk[3 * Np];
                         }
-                        T *o = sW + t * RG + ((el & 3) * Np + i) * SQ + c;
+                        T *o = ob + i * SQ;
                         o[0] = sig * (sig * (rx * ar[mt][r] + sx * as[mt][r]) + ax[mt][r]);
                         o[4] = sig * (sig * (ry * ar[mt][r] + sy * as[mt][r]) + ay[mt][r]);
                     }
@@ -666,20 +683,36 @@ __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) 
     __syncthreads();
     // coalesced copy out, one 16-byte vector per lane
     constexpr int VN = 8 / VW;   // vectors of a node
-    T *Qt = a.Q + k0 * Np * 8;
-    for (int z = tid; z < nel * Np * VN; z += kBlock) {
-        const int node = z / VN, h = z - node * VN, e = node / Np, i = node - e * Np;
-        const T *o = sW + (e >> 2) * RG + ((e & 3) * Np + i) * SQ + h * VW;
-        V16 v;
 #pragma unroll
-        for (int x = 0; x < VW; ++x) v[x] = o[x];
-        reinterpret_cast<V16 *>(Qt)[z] = v;
+    for (int v = 0; v < (EB * Np * VN + kBlock - 1) / kBlock; ++v) {
+        const unsigned z = tid + v * kBlock;
+        if (z < nel * Np * VN) {
+            const unsigned node = z / VN, h = z - node * VN, g = node / (4 * Np), i = node - g * (4 * Np);
+            const T *o = sW + g * RG + i * SQ + h * VW;
+            V16 q;
+#pragma unroll
+            for (int x = 0; x < VW; ++x) q[x] = o[x];
+            reinterpret_cast<V16 *>(Qt)[z] = q;
+        }
     }
 }
 
+// Waves per SIMD of the gradient: what the LDS of its blocks allows, at most 8
+// (FP64: its registers allow 4).
 template <typename T, int P>
-__global__ __launch_bounds__(kBlock) void k_avgrad(AvArgs<T> a) {
-    avgrad_body<T, P>(a, blockIdx.x);
+constexpr int grad_waves() {
+    using S = GradShape<T, P>;
+    constexpr int lds = (S::EB * kFields * S::Np + S::NT * S::RG + S::EB * 17) * int(sizeof(T));
+    constexpr int w = 160 * 1024 / lds, cap = sizeof(T) == 4 ? 8 : 4;
+    return w < cap ? (w < 1 ? 1 : w) : cap;
+}
+
+template <typename T, int P>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(grad_waves<T, P>()))) void k_avgrad(AvArgs<T> a) {
+    // each XCD (block b runs on XCD b % 8) takes a contiguous eighth of the mesh
+    const int chunk = gridDim.x / 8;
+    const int block = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
+    if (block < a.ngrad) avgrad_body<T, P>(a, block);
 }
 
 // Batched meshes of one order (FP32 viscous handles): work item = (job,
@@ -709,11 +742,12 @@ __global__ __launch_bounds__(kBlock) void k_sensor_elem_batch(const AvArgs<float
 }
 
 template <int P>
-__global__ __launch_bounds__(kBlock) void k_avgrad_batch(const AvArgs<float> *__restrict__ jobs,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(grad_waves<float, P>()))) void k_avgrad_batch(const AvArgs<float> *__restrict__ jobs,
                                                          const int2 *__restrict__ items,
                                                          const int *__restrict__ nitems_dev) {
-    const int w = int(blockIdx.x);
-    if (w >= *nitems_dev) return;
+    const int n = *nitems_dev, per = (n + 7) / 8, i = int(blockIdx.x / 8);
+    const int w = int(blockIdx.x % 8) * per + i;
+    if (i >= per || w >= n) return;
     const int2 it = items[w];
     avgrad_body<float, P>(jobs[it.x], it.y);
 }
@@ -1141,6 +1175,7 @@ AvArgs<T> av_args(const DevMesh &m) {
     AvArgs<T> a;
     a.K = m.K;
     a.P = m.P;
+    a.ngrad = grad_tiles(m);
     a.g = T(m.gamma);
     a.gamma = m.gamma;
     a.ff = make_farfield<T>(m.gamma, m.qinf);
@@ -1270,9 +1305,14 @@ int sensor_elem_blocks(const DevMesh &m) { return (m.K + kBlock - 1) / kBlock; }
 
 int av_tiles(const DevMesh &m) { return nblocks_rt(m.K, m.P); }
 
-static int grad_elements(int P) { return P == 1 ? 64 : (P == 2 ? 32 : 16); }
-
-int grad_tiles(const DevMesh &m) { return (m.K + grad_elements(m.P) - 1) / grad_elements(m.P); }
+int grad_tiles(const DevMesh &m) {
+    int eb = 16;   // elements per block
+    (void)with_order(m.P, [&](auto PC) {
+        eb = GradShape<float, decltype(PC)::value>::EB;   // the same in both precisions
+        return hipSuccess;
+    });
+    return (m.K + eb - 1) / eb;
+}
 
 // Fragments of the gradient's products (Dr, Ds, LIFT): lane l of fragment
 // z = ks MT + mt of an operator holds row 16 mt + l % 16, column 4 ks + l / 16
@@ -1290,7 +1330,6 @@ template <typename T>
 static void fill_opsG(int P, const double *Dr, const double *Ds, const double *LIFT, T *out) {
     (void)with_order(P, [&](auto PC) {
         using S = GradShape<T, decltype(PC)::value>;
-        static_assert(S::EB == (S::Nfp == 2 ? 64 : (S::Nfp == 3 ? 32 : 16)), "grad_elements");
         for (int z = 0; z < S::NG * 64 * 4; ++z) out[z] = T(0);
         const double *ops[3] = {Dr, Ds, LIFT};
         int first = 0;
@@ -1332,7 +1371,7 @@ hipError_t launch_av_batch(int P, bool cfl, const void *jobs, const void *items,
                                neitems_dev);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_avgrad_batch<PP>), dim3(gcapacity), dim3(kBlock), 0, st, j, git, ngitems_dev);
+        hipLaunchKernelGGL((k_avgrad_batch<PP>), dim3(unsigned((gcapacity + 7) / 8 * 8)), dim3(kBlock), 0, st, j, git, ngitems_dev);
         return hipGetLastError();
     });
 }
@@ -1345,7 +1384,7 @@ static hipError_t avgrad_t(const DevMesh &m, const void *U, const void *eps, voi
     a.Q = static_cast<T *>(Q);
     return with_order(m.P, [&](auto PC) {
         constexpr int P = decltype(PC)::value;
-        hipLaunchKernelGGL((k_avgrad<T, P>), dim3(grad_tiles(m)), dim3(kBlock), 0, st, a);
+        hipLaunchKernelGGL((k_avgrad<T, P>), dim3(unsigned((grad_tiles(m) + 7) / 8 * 8)), dim3(kBlock), 0, st, a);
         return hipGetLastError();
     });
 }
