@@ -326,12 +326,13 @@ int dg_mesh_setup(const dg_mesh_desc *d, void *stream, dg_mesh **out) {
     int rc = DG_OK;
     if ((rc = m->alloc(&nbr_d, size_t(K) * 3)) || (rc = m->alloc(&finfo_d, size_t(K))) ||
         (rc = m->alloc(&flag_d, 1)) || (rc = m->alloc(&count_d, 4)) ||
-        (rc = m->alloc(&x_d, size_t(K) * Np)) || (rc = m->alloc(&y_d, size_t(K) * Np)) ||
+        (rc = m->alloc(&x_d, size_t(K) * Np * 2)) ||
         (rc = m->alloc(&geo64, size_t(K) * 4 * Np)) || (rc = m->alloc(&fgeo64, size_t(K) * 9 * Nfp)) ||
         (rc = m->alloc(&wmass, size_t(K) * Np)) || (rc = m->alloc(&emax64, size_t(K))) ||
         (rc = m->alloc(&ops64, nops + size_t(Np) * Np)) || (rc = m->alloc(&scal, S_NSCAL)) ||
         (rc = m->alloc(&partial, size_t(partial_slots(K, P)) * 4 + 4)))
         return cleanup(rc);
+    y_d = x_d + size_t(K) * Np;
     dm.nbr = nbr_d;
     dm.finfo = finfo_d;
     dm.flag = flag_d;
@@ -383,20 +384,38 @@ int dg_mesh_setup(const dg_mesh_desc *d, void *stream, dg_mesh **out) {
                            " interior face nodes whose normal is not minus the neighbour's");
         return cleanup(DG_EGEOM);
     }
-    if (!dm.fp32 && !dm.weak && !dm.av) {
-        // an FP64 handle whose elements are all straight runs the stage's
-        // product on the FP64 matrix cores (k_stage_mfma64)
-        int *flags_d;
-        if ((rc = m->alloc(&flags_d, size_t(K)))) return cleanup(rc);
+    if (!dm.fp32 && !dm.weak && (!dm.av || P >= kMinMatrix64)) {
+        // the FP64 matrix-core stage (use_mfma64).  From P = 3 on the geometry
+        // records, the curved-element counts and the flags take the
+        // place of the node coordinates, which are not needed any more.
+        int *flags_d, *cpre_d = nullptr;
+        double *geoA64_d = nullptr;
+        if (P >= kMinMatrix64) {
+            geoA64_d = x_d;
+            cpre_d = reinterpret_cast<int *>(x_d + size_t(K) * 16);
+            flags_d = cpre_d + size_t(K) + 1;
+        } else if ((rc = m->alloc(&flags_d, size_t(K)))) {
+            return cleanup(rc);
+        }
         SETUP_TRY(launch_affine_flags(dm, flags_d, st));
         std::vector<int> flags(K);
         SETUP_TRY(hipMemcpyAsync(flags.data(), flags_d, sizeof(int) * K, hipMemcpyDeviceToHost, st));
         SETUP_TRY(hipStreamSynchronize(st));
-        if (std::all_of(flags.begin(), flags.end(), [](int f) { return f != 0; })) {
+        std::vector<int> cpre(size_t(K) + 1);
+        int Kc = 0;
+        for (long k = 0; k < K; ++k) {
+            cpre[k] = Kc;
+            Kc += flags[k] ? 0 : 1;
+        }
+        cpre[K] = Kc;
+        if (use_mfma64(P, dm.av, K, Kc)) {
             const size_t nA = mfma64_opsA_values(P);
-            double *opsA64_d, *geoA64_d;
-            if ((rc = m->alloc(&opsA64_d, nA)) || (rc = m->alloc(&geoA64_d, size_t(K) * 16))) return cleanup(rc);
-            SETUP_TRY(launch_pack_affine64(dm, geoA64_d, st));
+            double *opsA64_d;
+            if ((rc = m->alloc(&opsA64_d, nA))) return cleanup(rc);
+            if (!geoA64_d && (rc = m->alloc(&geoA64_d, size_t(K) * 16))) return cleanup(rc);
+            SETUP_TRY(launch_pack_affine64(dm, flags_d, geoA64_d, st));
+            if (cpre_d)
+                SETUP_TRY(hipMemcpyAsync(cpre_d, cpre.data(), sizeof(int) * cpre.size(), hipMemcpyHostToDevice, st));
             std::vector<double> opsA64(nA);
             mfma64_fill_opsA(P, ref.Dr.data(), ref.Ds.data(), ref.LIFT.data(), opsA64.data());
             SETUP_TRY(hipMemcpyAsync(opsA64_d, opsA64.data(), sizeof(double) * nA, hipMemcpyHostToDevice, st));
@@ -406,6 +425,8 @@ int dg_mesh_setup(const dg_mesh_desc *d, void *stream, dg_mesh **out) {
             SETUP_TRY(hipStreamSynchronize(st));
             dm.opsA64 = opsA64_d;
             dm.geoA64 = geoA64_d;
+            dm.cpre = cpre_d;
+            dm.Kc = Kc;
             dm.vmax = vmax64_d;
         }
     }
@@ -690,7 +711,7 @@ static int step_fused64(dg_mesh *m, void *U, void *work, double dt, hipStream_t 
     HIP_TRY(launch_dt_slots64(m->dm, dt, st));
     for (int s = 0; s < 5; ++s) {
         HIP_TRY(m->time_begin(st));
-        HIP_TRY(launch_stage_mfma64(m->dm, in[s], out[s], R, nullptr, s, s == 4, st));
+        HIP_TRY(launch_stage_mfma64(m->dm, in[s], out[s], R, nullptr, s, s == 4, nullptr, st));
         HIP_TRY(m->time_end(st));
     }
     return DG_OK;

@@ -10,6 +10,13 @@ namespace dg {
 
 constexpr int kFields = 4;  // rho, rho u, rho v, E
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+// 16-byte accesses to caller buffers, which need only be aligned to a value
+typedef float f32v16 __attribute__((ext_vector_type(4), aligned(4)));
+typedef double f64v16 __attribute__((ext_vector_type(2), aligned(8)));
+
 template <int P>
 struct Order {
     static constexpr int Np = (P + 1) * (P + 2) / 2;
@@ -283,6 +290,20 @@ __device__ inline void wall_visc_jump(const T gm[kFields], T nx, T ny, T d[kFiel
     d[2] = gn * ny - gm[2];
     d[3] = -gm[3];
 }
+
+// Block order of the stage kernels: block b runs on XCD b % 8, and each XCD
+// takes a contiguous run of `chunk` tiles, so that a tile's neighbours are
+// mostly in that XCD's own L2 (the viscous gradient of 120,000 elements at
+// P = 3 reads 29 instead of 67 MB).  chunk comes with the kernel's arguments
+// (the grid size would be one more dependent load before the first address);
+// 0: tiles in block order.  The grid is a multiple of 8; surplus blocks get a
+// tile past the end.
+__device__ __forceinline__ int xcd_tile(int chunk) {
+    const int b = int(blockIdx.x);
+    return chunk > 0 ? (b % 8) * chunk + b / 8 : b;
+}
+inline int xcd_chunk(long tiles) { return int((tiles + 7) / 8); }
+inline unsigned xcd_grid(long tiles) { return unsigned((tiles + 7) / 8 * 8); }
 
 // Carpenter-Kennedy 2N-storage (5,4) coefficients.
 __host__ __device__ inline double rk_a(int s) {

@@ -1,6 +1,8 @@
-// HIP kernels of the nodal DG Euler solver for gfx950 (VALU path).
+// HIP kernels of the nodal DG Euler solver for gfx950: the VALU stage (the
+// FP64 handles that use_mfma64 leaves to it), sensor, viscous gradient,
+// geometry, reductions, prolongation.
 //
-// Tiling: one 64-lane wavefront holds EW = floor(64/Np) whole elements, one
+// Tiling of the VALU stage: one 64-lane wavefront holds EW = floor(64/Np) whole elements, one
 // lane per node (lane = element * Np + node); a 256-thread block holds four
 // wavefronts.  Elements never straddle wavefronts.  The element's state,
 // fluxes and scaled face-flux jumps are staged in LDS; each lane keeps its
@@ -25,6 +27,7 @@ constexpr int kBlock = 256;
 template <typename T>
 struct StageArgs {
     int K, stage, mode;
+    int chunk;     // tiles of an XCD (xcd_tile)
     int riemann;   // numerical flux: RIEMANN_LF or RIEMANN_HLLC
     T g, ra, rb;
     FarField<T> ff;
@@ -97,7 +100,7 @@ __global__ __launch_bounds__(kBlock) void k_stage(StageArgs<T> a) {
     __shared__ T sOps[NOPS];
     LdsCopy<T, NOPS> opsc;
     opsc.load(a.ops);
-    Tile<P> t(a.K);
+    Tile<P> t(a.K, xcd_tile(a.chunk));
     const long k = t.k;
     const int i = t.i, el = t.el;
 
@@ -271,7 +274,7 @@ __global__ __launch_bounds__(kBlock) void k_stage(StageArgs<T> a) {
 template <typename T>
 struct AvArgs {
     int K, P;
-    int ngrad;      // blocks of the gradient
+    int ngrad, gchunk;   // tiles of the gradient, and of an XCD (xcd_tile)
     T g;
     double gamma;   // the time-step bound is formed in FP64
     FarField<T> ff;
@@ -480,11 +483,6 @@ struct GradShape {
     static constexpr int NV = (EB * kFields * Np / VW + kBlock - 1) / kBlock;   // 16-byte vectors per thread
 };
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-// 16-byte accesses to caller buffers, which need only be aligned to a value
-typedef float f32v16 __attribute__((ext_vector_type(4), aligned(4)));
-typedef double f64v16 __attribute__((ext_vector_type(2), aligned(8)));
 template <typename T>
 struct Vec;
 template <>
@@ -709,10 +707,8 @@ constexpr int grad_waves() {
 
 template <typename T, int P>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(grad_waves<T, P>()))) void k_avgrad(AvArgs<T> a) {
-    // each XCD (block b runs on XCD b % 8) takes a contiguous eighth of the mesh
-    const int chunk = gridDim.x / 8;
-    const int block = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
-    if (block < a.ngrad) avgrad_body<T, P>(a, block);
+    const int tile = xcd_tile(a.gchunk);
+    if (tile < a.ngrad) avgrad_body<T, P>(a, tile);
 }
 
 // Batched meshes of one order (FP32 viscous handles): work item = (job,
@@ -1160,13 +1156,19 @@ hipError_t stage_t(const DevMesh &m, const void *Uin, void *Uout, void *R, void 
     a.ops = tbl_ops<T>(m);
     a.dt = m.scal + S_DT;
     a.Q = static_cast<const T *>(Q);
+    // (the orders and viscosity that use_mfma64 leaves to this kernel)
     return with_order(m.P, [&](auto PC) {
         constexpr int P = decltype(PC)::value;
-        if (m.av)
-            hipLaunchKernelGGL((k_stage<T, P, true>), dim3(nblocks<P>(m.K)), dim3(kBlock), 0, st, a);
-        else
-            hipLaunchKernelGGL((k_stage<T, P, false>), dim3(nblocks<P>(m.K)), dim3(kBlock), 0, st, a);
-        return hipGetLastError();
+        const dim3 grid(xcd_grid(nblocks<P>(m.K)));
+        a.chunk = xcd_chunk(nblocks<P>(m.K));
+        if constexpr (P != 3) {
+            if (m.av)
+                hipLaunchKernelGGL((k_stage<T, P, true>), grid, dim3(kBlock), 0, st, a);
+            else
+                hipLaunchKernelGGL((k_stage<T, P, false>), grid, dim3(kBlock), 0, st, a);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
     });
 }
 
@@ -1176,6 +1178,7 @@ AvArgs<T> av_args(const DevMesh &m) {
     a.K = m.K;
     a.P = m.P;
     a.ngrad = grad_tiles(m);
+    a.gchunk = xcd_chunk(a.ngrad);
     a.g = T(m.gamma);
     a.gamma = m.gamma;
     a.ff = make_farfield<T>(m.gamma, m.qinf);
@@ -1253,11 +1256,11 @@ hipError_t launch_cast(const double *src, float *dst, size_t n, hipStream_t st) 
 hipError_t launch_stage(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs, int stage,
                         const void *Q, hipStream_t st) {
     // the weak form: its own kernel; FP32 (with or without viscosity): the
-    // matrix-core kernel; FP64: the FP64 matrix cores for a mesh of straight
-    // elements without viscosity, else VALU
+    // matrix-core kernel; FP64: the FP64 matrix cores where use_mfma64 says
+    // so, else VALU
     if (m.weak) return launch_stage_weak(m, Uin, Uout, R, rhs, stage, st);
     if (m.fp32) return launch_stage_mfma(m, Uin, Uout, R, rhs, stage, MfmaStep(), st, Q);
-    if (m.opsA64 && !m.av) return launch_stage_mfma64(m, Uin, Uout, R, rhs, stage, false, st);
+    if (m.opsA64) return launch_stage_mfma64(m, Uin, Uout, R, rhs, stage, false, Q, st);
     return stage_t<double>(m, Uin, Uout, R, rhs, stage, Q, st);
 }
 
@@ -1384,7 +1387,7 @@ static hipError_t avgrad_t(const DevMesh &m, const void *U, const void *eps, voi
     a.Q = static_cast<T *>(Q);
     return with_order(m.P, [&](auto PC) {
         constexpr int P = decltype(PC)::value;
-        hipLaunchKernelGGL((k_avgrad<T, P>), dim3(unsigned((grad_tiles(m) + 7) / 8 * 8)), dim3(kBlock), 0, st, a);
+        hipLaunchKernelGGL((k_avgrad<T, P>), dim3(xcd_grid(grad_tiles(m))), dim3(kBlock), 0, st, a);
         return hipGetLastError();
     });
 }

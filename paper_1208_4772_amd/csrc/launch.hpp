@@ -62,8 +62,8 @@ struct DevMesh {
     const int *cpre = nullptr;      // [K + 1] number of curved elements before element k
     const float *geoC = nullptr;    // [Kc][4 Np + 9 Nfp] curved geometry
     const float *opsA = nullptr;    // MFMA A operand table
-    const double *opsA64 = nullptr; // FP64 handles of straight elements without viscosity: the
-                                    // FP64 matrix-core stage's A operand (null: the VALU stage)
+    const double *opsA64 = nullptr; // FP64 matrix-core stage's A operand (null: the VALU stage,
+                                    // use_mfma64)
     const float *opsG = nullptr;    // viscous handles: fragments of the gradient's operators
     const double *opsG64 = nullptr;
     const double *geoA64 = nullptr; // ... and its [K][16] geometry records (k_pack_affine64)
@@ -80,6 +80,22 @@ struct DevMesh {
     int npartial = 0;
 };
 
+// Which FP64 nodal handles run their stage on the matrix cores (the others on
+// the VALUs).  Straight meshes without viscosity always.  With viscosity or
+// curved elements from P = 3 on: below it the contractions are short and the
+// records would need memory of their own (from P = 3 on they take the place
+// of the node coordinates).  A small mesh's stage time is the latency of one
+// tile, and the padded rows make the matrix cores' chain the longer one at
+// P = 4 and 5 (us a step, VALU / matrix cores: cylinder at P = 5 50 / 60 for
+// 1,500 elements, 83 / 75 for 8,000; viscous airfoil at P = 5 123 / 140 for
+// 1,500, 188 / 184 for 8,000; P = 4 43 / 45 for 1,100, viscous 108 / 105 for
+// 1,500).  Large: 80,000-element cylinder at P = 4, an rhs 56 / 42 us;
+// viscous airfoil, 60,000 at P = 4, 512 / 389 us a step.
+constexpr int kMinMatrix64 = 3;
+inline bool use_mfma64(int P, bool av, long K, long curved) {
+    if (!av && curved == 0) return true;
+    return P >= kMinMatrix64 && K >= (P == 5 ? 6144 : (P == 4 ? 2048 : 0));
+}
 // FP64 stage on the matrix cores (stage64.hip): A operand [LIFT -Dr -Ds] in
 // lane order, and the launch
 size_t mfma64_opsA_values(int P);
@@ -87,10 +103,10 @@ void mfma64_fill_opsA(int P, const double *Dr, const double *Ds, const double *L
 // bound: a run's step-closing stage, which also reduces the next step's
 // time-step bound into m.vmax (first kVmaxSlots slots) and checks the state
 hipError_t launch_stage_mfma64(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs, int stage,
-                               bool bound, hipStream_t st);
+                               bool bound, const void *Q, hipStream_t st);
 // dt from the bound in m.vmax's slots (or the fixed step); clears them
 hipError_t launch_dt_slots64(const DevMesh &m, double dt_fixed, hipStream_t st);
-hipError_t launch_pack_affine64(const DevMesh &m, double *rec, hipStream_t st);
+hipError_t launch_pack_affine64(const DevMesh &m, const int *straight, double *rec, hipStream_t st);
 
 // offsets of the operators in the ops tables
 inline size_t ops_size(int Np, int Nfp) { return size_t(Np) * Np * 3 + size_t(Np) * 3 * Nfp; }

@@ -1,5 +1,4 @@
-// FP64 stage kernel on the matrix cores (v_mfma_f64_16x16x4f64) for handles
-// whose elements are all straight and carry no artificial viscosity.
+// FP64 stage kernel on the matrix cores (v_mfma_f64_16x16x4f64).
 //
 // With constant metric terms the volume term folds into the fluxes,
 //   -(r_x Dr F + s_x Ds F + r_y Dr G + s_y Ds G) = -Dr F' - Ds G',
@@ -14,7 +13,18 @@
 // first node, one value for the whole element or face as the fold assumes
 // (the per-node values of a straight element differ by rounding only, which
 // Dr and Ds would amplify on small elements).  Boundary faces take the ghost
-// states of the VALU kernel, and either numerical flux.
+// states, and either numerical flux.
+//
+// A tile with a curved element (CURV, a block-uniform test) keeps the fluxes
+// unfolded: -Dr F, -Ds F, -Dr G and -Ds G are four products, each scaled row
+// by row with the per-node metric term and added up, and the faces take the
+// per-face-node normals and Fscale.  Twice the volume products, on the tiles
+// along the walls only; their operator fragments come from LDS and the next
+// product's metric terms are requested before each product (requested from
+// the caches one after the other they were the tile's latency: 60,000 curved
+// elements at P = 3, ten steps, 1.75 ms without, 1.64 with, VALU kernel
+// 1.77).  Viscous handles (AV) subtract sigma Q from the fluxes and add the
+// viscous face terms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -25,9 +35,6 @@
 
 namespace dg {
 namespace {
-
-typedef double f64x4_t __attribute__((ext_vector_type(4)));
-typedef double f64x2_t __attribute__((ext_vector_type(2)));
 
 template <int P>
 struct Tri64 {
@@ -61,8 +68,12 @@ struct Stage64Args {
     double *__restrict__ rhs;
     const int *__restrict__ nbr;       // [K][3]
     const int *__restrict__ finfo;     // [K] packed neighbour face and bc codes
-    const double *__restrict__ rec;    // [K][16] r_x s_x r_y s_y | (n_x n_y Fscale) x 3 | 0 0 0
-    const f64x4_t *__restrict__ opsA;  // [3][NG][64]: LIFT, -Dr, -Ds fragments; lane l of
+    int chunk;                         // tiles of an XCD (xcd_tile)
+    const double *__restrict__ rec;    // [K][16] r_x s_x r_y s_y | (n_x n_y Fscale) x 3 | curved 0 0
+    const double *__restrict__ geo;    // [K][4][Np] per-node metric terms (curved tiles)
+    const int *__restrict__ cpre;      // [K + 1] curved elements before element k (meshes with curved elements)
+    const f64v16 *__restrict__ Q;      // [K][Np][4] sigma Q, x then y parts of the four fields (viscous handles)
+    const f64x4 *__restrict__ opsA;  // [3][NG][64]: LIFT, -Dr, -Ds fragments; lane l of
                                        // fragment z = ks MT + mt: slot z % 4 of group z / 4
     const double *__restrict__ dt;
     // the last stage of a step in a run: also the next step's time-step
@@ -76,31 +87,50 @@ struct Stage64Args {
 
 // five waves per SIMD (at most 96 registers): 901 us on the 1M-element
 // P = 5 mesh, against 1,003 us at the four the default register budget gives
-// and 1,151 us at six (which spills)
-template <int P>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_stage_mfma64(Stage64Args a) {
+// and 1,151 us at six (which spills).  Viscous handles take
+// four (K = 30,000 at P = 3: 2.23 ms a run of ten steps against 2.25 at five),
+// the curved variant four at P = 5, where five spill.
+template <int P, bool AV, bool CURV>
+constexpr int waves64() {
+    return AV || (P == 5 && CURV) ? 4 : 5;
+}
+
+template <int P, bool AV, bool CURV>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves64<P, AV, CURV>()))) void k_stage_mfma64(Stage64Args a) {
     using S = Tri64<P>;
     constexpr int Np = S::Np, Nfp = S::Nfp, NF3 = S::NF3, KSD = S::KSD, KSL = S::KSL, KPP = S::KPP;
     constexpr int MT = S::MT, NG = S::NG, W = S::W, NTH = S::NTH, NT = S::NT, EB = S::EB;
     constexpr int TPT = S::TPT, PPT = S::PPT, NV = S::NV;
     __shared__ __attribute__((aligned(16))) double sB[NT][16][KPP];
     __shared__ __attribute__((aligned(16))) double sU[EB * kFields * Np];
-    const long k0 = (long)blockIdx.x * EB;
+    const long k0 = (long)xcd_tile(a.chunk) * EB;
+    if (k0 >= a.K) return;
     const int nel = (int)min((long)EB, (long)a.K - k0);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long base = k0 * kFields * Np;   // even: EB is a multiple of 16
+    const long base = k0 * kFields * Np;
     const int nflt = nel * kFields * Np;
     const int nv = nflt / 2;
     const int ntask = nel * NF3;
+    // whether the tile holds a curved element
+    bool curved = false;
+    if constexpr (CURV) curved = a.cpre[k0 + nel] != a.cpre[k0];
+    // the -Dr and -Ds fragments of a curved tile's four products, staged once
+    __shared__ __attribute__((aligned(16))) f64x4 sA[CURV ? 2 * NG * 64 : 1];
+    constexpr int NAV = (2 * NG * 64 + NTH - 1) / NTH;
+    f64x4 av[CURV ? NAV : 1];
+    if (CURV && curved) {
+#pragma unroll
+        for (int v = 0; v < NAV; ++v) av[CURV ? v : 0] = a.opsA[NG * 64 + min(tid + v * NTH, 2 * NG * 64 - 1)];
+    }
 
     // ---- loads: the tile, then the neighbour traces of this thread's
     // face-node tasks (task = element * 3 Nfp + face node; a boundary task
     // reads its own element and ignores it)
-    const f64x2_t *Uv = reinterpret_cast<const f64x2_t *>(a.Uin + base);
+    const f64v16 *Uv = reinterpret_cast<const f64v16 *>(a.Uin + base);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
         const int z = tid + v * NTH;
-        if (z < nv) reinterpret_cast<f64x2_t *>(sU)[z] = Uv[z];
+        if (z < nv) reinterpret_cast<f64x2 *>(sU)[z] = Uv[z];
     }
     for (int z = 2 * nv + tid; z < nflt; z += NTH) sU[z] = a.Uin[base + z];
     int infov[TPT];
@@ -117,15 +147,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 #pragma unroll
         for (int c = 0; c < kFields; ++c) upn[t][c] = a.Uin[(kn * kFields + c) * Np + vp];
     }
+    if (CURV && curved) {
+#pragma unroll
+        for (int v = 0; v < NAV; ++v)
+            if (tid + v * NTH < 2 * NG * 64) sA[tid + v * NTH] = av[CURV ? v : 0];
+    }
     __syncthreads();
 
-    f64x4_t acc[MT];
+    f64x4 acc[MT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[mt] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-    f64x4_t ga[NG];
+    for (int mt = 0; mt < MT; ++mt) acc[mt] = f64x4{0.0, 0.0, 0.0, 0.0};
+    f64x4 ga[NG];
+    auto load_A = [&](int pass) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) ga[g] = a.opsA[(pass * NG + g) * 64 + lane];
+    };
     // one pass of the product over the wavefront's column group: B rows
     // [0, 4 KSN) against the pass's A fragments
-    auto product = [&](auto KSC) {
+    auto product = [&](f64x4(&out)[MT], auto KSC) {
         constexpr int KSN = decltype(KSC)::value;
         const int t = wave;
         if (4 * t < nel) {
@@ -135,7 +174,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
                     const int z = ks * MT + mt;
-                    acc[mt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[z / 4][z % 4], b, acc[mt], 0, 0, 0);
+                    out[mt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[z / 4][z % 4], b, out[mt], 0, 0, 0);
                 }
             }
         }
@@ -159,8 +198,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
             double um[kFields], up[kFields], d[kFields];
 #pragma unroll
             for (int c = 0; c < kFields; ++c) um[c] = sU[(e * kFields + c) * Np + vm];
-            const double *rc = a.rec + k * 16 + 4 + 3 * f;
-            const double nx = rc[0], ny = rc[1], fs = rc[2];
+            double nx, ny, fs;
+            if (CURV && curved) {
+                const double *gf = a.fgeo + k * 3 * NF3 + q;
+                nx = gf[0];
+                ny = gf[NF3];
+                fs = gf[2 * NF3];
+            } else {
+                const double *rc = a.rec + k * 16 + 4 + 3 * f;
+                nx = rc[0];
+                ny = rc[1];
+                fs = rc[2];
+            }
             const int code = face_bc(infov[t], f);
             if (code == BC_INTERIOR) {
 #pragma unroll
@@ -169,19 +218,41 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
                 ghost_state(a.g, code, um, nx, ny, a.ff, up);
             }
             flux_jump(a.riemann, a.g, um, up, nx, ny, d);
+            if constexpr (AV) {
+                // (sigma Q)*.n - (sigma Q)-.n: the central value inside, the
+                // mirror closure at a wall, zero at the far field
+                if (code != BC_FARFIELD) {
+                    auto normal = [&](const f64v16 *q8, double(&v)[kFields]) {
+#pragma unroll
+                        for (int c = 0; c < kFields; ++c) v[c] = nx * q8[c / 2][c % 2] + ny * q8[2 + c / 2][c % 2];
+                    };
+                    double vm4[kFields], vj[kFields];
+                    normal(a.Q + (k * Np + vm) * 4, vm4);
+                    if (code == BC_INTERIOR) {
+                        const int vp = face_node(P, face_nbr_face(infov[t], f), Nfp - 1 - j);
+                        double vp4[kFields];
+                        normal(a.Q + ((long)a.nbr[k * 3 + f] * Np + vp) * 4, vp4);
+#pragma unroll
+                        for (int c = 0; c < kFields; ++c) vj[c] = 0.5 * (vm4[c] + vp4[c]) - vm4[c];
+                    } else {
+                        wall_visc_jump(vm4, nx, ny, vj);
+                    }
+#pragma unroll
+                    for (int c = 0; c < kFields; ++c) d[c] += vj[c];
+                }
+            }
             double(*B)[KPP] = sB[e / 4];
             const int col = (e % 4) * kFields;
 #pragma unroll
             for (int c = 0; c < kFields; ++c) B[col + c][q] = fs * d[c];
         }
     }
-#pragma unroll
-    for (int g = 0; g < NG; ++g) ga[g] = a.opsA[g * 64 + lane];
-    // the pointwise fluxes of this thread's nodes, kept for both directions
-    double Fv[PPT][kFields], Gv[PPT][kFields];
-#pragma unroll
-    for (int p = 0; p < PPT; ++p) {
-        const int z = min(tid + p * NTH, nel * Np - 1);
+    load_A(0);
+    // the pointwise fluxes of this thread's nodes: kept in registers for both
+    // directions, or (the curved variant, which needs the registers; with
+    // viscosity only at P = 5, as it would read sigma Q again) formed again
+    // for each pass
+    auto fluxes = [&](int z, double(&F)[kFields], double(&G)[kFields]) {
         const int el = z / Np, i = z - el * Np;
         double u[kFields];
 #pragma unroll
@@ -189,23 +260,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
         const double ir = rcp(u[0]);
         const double vx = u[1] * ir, vy = u[2] * ir;
         const double pr = pressure_ir(a.g, u, ir);
-        Fv[p][0] = u[1];
-        Fv[p][1] = u[1] * vx + pr;
-        Fv[p][2] = u[2] * vx;
-        Fv[p][3] = (u[3] + pr) * vx;
-        Gv[p][0] = u[2];
-        Gv[p][1] = u[1] * vy;
-        Gv[p][2] = u[2] * vy + pr;
-        Gv[p][3] = (u[3] + pr) * vy;
+        F[0] = u[1];
+        F[1] = u[1] * vx + pr;
+        F[2] = u[2] * vx;
+        F[3] = (u[3] + pr) * vx;
+        G[0] = u[2];
+        G[1] = u[1] * vy;
+        G[2] = u[2] * vy + pr;
+        G[3] = (u[3] + pr) * vy;
+        if constexpr (AV) {
+            const f64v16 *Qe = a.Q + (k0 * Np + z) * 4;
+#pragma unroll
+            for (int c = 0; c < kFields; ++c) {
+                F[c] -= Qe[c / 2][c % 2];
+                G[c] -= Qe[2 + c / 2][c % 2];
+            }
+        }
+    };
+    constexpr bool kKeep = !CURV || (AV && P < 5);
+    double Fv[kKeep ? PPT : 1][kFields], Gv[kKeep ? PPT : 1][kFields];
+    if constexpr (kKeep) {
+#pragma unroll
+        for (int p = 0; p < PPT; ++p) fluxes(min(tid + p * NTH, nel * Np - 1), Fv[p], Gv[p]);
     }
     __syncthreads();
-    product(std::integral_constant<int, KSL>());
+    product(acc, std::integral_constant<int, KSL>());
 
-    // ---- the two directions: F' = r_x F + r_y G, then G' = s_x F + s_y G,
-    // in rows i < Np (rows Np .. 4 KSD zero)
-#pragma unroll
-    for (int dir = 0; dir < 2; ++dir) {
-        __syncthreads();
+    // the two volume passes fill rows i < Np of the B buffer (rows Np ..
+    // 4 KSD zero)
+    auto pad_rows = [&]() {
         if constexpr (4 * KSD > Np) {
             constexpr int PADR = 4 * KSD - Np, PADN = 16 * PADR;
             for (int z = tid; z < NT * PADN; z += NTH) {
@@ -213,24 +296,94 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
                 sB[t][rem / PADR][Np + rem % PADR] = 0.0;
             }
         }
+    };
+    if (!(CURV && curved)) {
+        // ---- the two directions: F' = r_x F + r_y G, then G' = s_x F + s_y G
 #pragma unroll
-        for (int p = 0; p < PPT; ++p) {
-            const int z = tid + p * NTH;
-            if (z < nel * Np) {
-                const int el = z / Np, i = z - el * Np;
-                const long k = k0 + el;
-                // r_x, r_y for F'; s_x, s_y for G'
-                const double mf = a.rec[k * 16 + dir], mg = a.rec[k * 16 + 2 + dir];
-                double(*B)[KPP] = sB[el / 4];
-                const int col = (el % 4) * kFields;
+        for (int dir = 0; dir < 2; ++dir) {
+            __syncthreads();
+            pad_rows();
 #pragma unroll
-                for (int c = 0; c < kFields; ++c) B[col + c][i] = mf * Fv[p][c] + mg * Gv[p][c];
+            for (int p = 0; p < PPT; ++p) {
+                const int z = tid + p * NTH;
+                if (z < nel * Np) {
+                    const int el = z / Np, i = z - el * Np;
+                    const long k = k0 + el;
+                    // r_x, r_y for F'; s_x, s_y for G'
+                    const double mf = a.rec[k * 16 + dir], mg = a.rec[k * 16 + 2 + dir];
+                    double(*B)[KPP] = sB[el / 4];
+                    const int col = (el % 4) * kFields;
+                    if constexpr (!kKeep) fluxes(z, Fv[0], Gv[0]);
+                    constexpr int one = kKeep ? 1 : 0;
+#pragma unroll
+                    for (int c = 0; c < kFields; ++c) B[col + c][i] = mf * Fv[one * p][c] + mg * Gv[one * p][c];
+                }
             }
+            load_A(1 + dir);
+            __syncthreads();
+            product(acc, std::integral_constant<int, KSD>());
         }
+    } else {
+        // ---- F, then G: -Dr and -Ds of each, scaled by the metric terms of
+        // the rows this lane holds
+        const int le = 4 * wave + ((lane & 15) >> 2);
+        const double *gk = a.geo + (k0 + min(le, nel - 1)) * 4 * Np;
+        auto metrics = [&](double(&g)[MT][4], int m) {   // r_x, s_x, r_y, s_y
 #pragma unroll
-        for (int g = 0; g < NG; ++g) ga[g] = a.opsA[((1 + dir) * NG + g) * 64 + lane];
-        __syncthreads();
-        product(std::integral_constant<int, KSD>());
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) g[mt][r] = gk[m * Np + min(16 * mt + (lane >> 4) + 4 * r, Np - 1)];
+        };
+        double g[MT][4], gn[MT][4];
+        metrics(g, 0);
+#pragma unroll 1
+        for (int m = 0; m < 4; ++m) {
+            const int flux = m >> 1;
+            if (!(m & 1)) {
+                __syncthreads();
+                pad_rows();
+#pragma unroll
+                for (int p = 0; p < PPT; ++p) {
+                    const int z = tid + p * NTH;
+                    if (z < nel * Np) {
+                        const int el = z / Np, i = z - el * Np;
+                        double(*B)[KPP] = sB[el / 4];
+                        const int col = (el % 4) * kFields;
+                        if constexpr (!kKeep) fluxes(z, Fv[0], Gv[0]);
+                        constexpr int one = kKeep ? 1 : 0;
+#pragma unroll
+                        for (int c = 0; c < kFields; ++c) B[col + c][i] = flux ? Gv[one * p][c] : Fv[one * p][c];
+                    }
+                }
+                __syncthreads();
+            }
+            // the next operator's metric terms on their way during the product
+            metrics(gn, min(m + 1, 3));
+            f64x4 part[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) part[mt] = f64x4{0.0, 0.0, 0.0, 0.0};
+            if (4 * wave < nel) {
+                const f64x4 *A = sA + (m & 1) * NG * 64 + lane;
+                f64x4 a4;
+#pragma unroll
+                for (int ks = 0; ks < KSD; ++ks) {
+                    const double b = sB[wave][lane & 15][4 * ks + (lane >> 4)];
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        const int z = ks * MT + mt;
+                        if (z % 4 == 0) a4 = A[z / 4 * 64];
+                        part[mt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a4[z % 4], b, part[mt], 0, 0, 0);
+                    }
+                }
+            }
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    acc[mt][r] += g[mt][r] * part[mt][r];
+                    g[mt][r] = gn[mt][r];
+                }
+        }
     }
     __syncthreads();
     // the result over the wavefront's own B block as [element % 4][field][node]
@@ -262,16 +415,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     for (int v = 0; v < NV; ++v) {
         const int zv = tid + v * NTH;
         if (zv < nv) {
-            const f64x2_t rh = {result(2 * zv), result(2 * zv + 1)};
+            const f64x2 rh = {result(2 * zv), result(2 * zv + 1)};
             if (a.mode == 0) {
-                reinterpret_cast<f64x2_t *>(a.rhs + base)[zv] = rh;
+                reinterpret_cast<f64v16 *>(a.rhs + base)[zv] = rh;
             } else {
-                const f64x2_t rold = rk_read ? reinterpret_cast<const f64x2_t *>(a.R + base)[zv] : f64x2_t{0.0, 0.0};
-                const f64x2_t rr = a.stage == 0 ? dt * rh : a.ra * rold + dt * rh;
-                const f64x2_t un = reinterpret_cast<const f64x2_t *>(sU)[zv] + a.rb * rr;
-                reinterpret_cast<f64x2_t *>(a.R + base)[zv] = rr;
-                reinterpret_cast<f64x2_t *>(a.Uout + base)[zv] = un;
-                if (a.bound) reinterpret_cast<f64x2_t *>(sU)[zv] = un;
+                const f64x2 rold = rk_read ? f64x2(reinterpret_cast<const f64v16 *>(a.R + base)[zv]) : f64x2{0.0, 0.0};
+                const f64x2 rr = a.stage == 0 ? dt * rh : a.ra * rold + dt * rh;
+                const f64x2 un = reinterpret_cast<const f64x2 *>(sU)[zv] + a.rb * rr;
+                reinterpret_cast<f64v16 *>(a.R + base)[zv] = rr;
+                reinterpret_cast<f64v16 *>(a.Uout + base)[zv] = un;
+                if (a.bound) reinterpret_cast<f64x2 *>(sU)[zv] = un;
             }
         }
     }
@@ -346,9 +499,12 @@ __global__ void k_dt_slots64(double cfl, double dt_fixed, unsigned long long *__
     scal[S_STEPS] += 1.0;
 }
 
-// The 128-byte geometry record of each (straight) element.
+// The 128-byte geometry record of each element: the metric terms at its
+// first node, each face's normal and Fscale at its first node, and 1 in slot
+// 13 for a curved element (whose per-node tables are used instead).
 __global__ void k_pack_affine64(int K, int Np, int Nfp, const double *__restrict__ geo,
-                                const double *__restrict__ fgeo, double *__restrict__ rec) {
+                                const double *__restrict__ fgeo, const int *__restrict__ straight,
+                                double *__restrict__ rec) {
     const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= K) return;
     const int NF3 = 3 * Nfp;
@@ -356,7 +512,8 @@ __global__ void k_pack_affine64(int K, int Np, int Nfp, const double *__restrict
     for (int m = 0; m < 4; ++m) r[m] = geo[(k * 4 + m) * Np];
     for (int f = 0; f < 3; ++f)
         for (int m = 0; m < 3; ++m) r[4 + 3 * f + m] = fgeo[(k * 3 + m) * NF3 + f * Nfp];
-    r[13] = r[14] = r[15] = 0.0;
+    r[13] = straight[k] ? 0.0 : 1.0;
+    r[14] = r[15] = 0.0;
 }
 
 template <typename F>
@@ -402,9 +559,9 @@ void mfma64_fill_opsA(int P, const double *Dr, const double *Ds, const double *L
     });
 }
 
-hipError_t launch_pack_affine64(const DevMesh &m, double *rec, hipStream_t st) {
+hipError_t launch_pack_affine64(const DevMesh &m, const int *straight, double *rec, hipStream_t st) {
     hipLaunchKernelGGL(k_pack_affine64, dim3((m.K + 127) / 128), dim3(128), 0, st, m.K, m.Np, m.Nfp, m.geo64,
-                       m.fgeo64, rec);
+                       m.fgeo64, straight, rec);
     return hipGetLastError();
 }
 
@@ -414,7 +571,8 @@ hipError_t launch_dt_slots64(const DevMesh &m, double dt_fixed, hipStream_t st) 
 }
 
 hipError_t launch_stage_mfma64(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs, int stage,
-                               bool bound, hipStream_t st) {
+                               bool bound, const void *Q, hipStream_t st) {
+    if (m.av && !Q) return hipErrorInvalidValue;
     Stage64Args a;
     a.K = m.K;
     a.stage = stage;
@@ -431,7 +589,15 @@ hipError_t launch_stage_mfma64(const DevMesh &m, const void *Uin, void *Uout, vo
     a.nbr = m.nbr;
     a.finfo = m.finfo;
     a.rec = m.geoA64;
-    a.opsA = reinterpret_cast<const f64x4_t *>(m.opsA64);
+    a.geo = m.geo64;
+    a.cpre = m.cpre;
+    a.Q = static_cast<const f64v16 *>(Q);
+    // XCD-contiguous tiles while a stage's buffers stay in the last-level
+    // cache (20,000 elements at P = 3: 1,374 -> 1,249 us a run of 20 steps);
+    // beyond it consecutive blocks on consecutive tiles stream better
+    // (300,000 at P = 5: 14.5 against 15.1 ms)
+    const bool in_cache = 4 * size_t(m.K) * kFields * m.Np * sizeof(double) <= (size_t(256) << 20);
+    a.opsA = reinterpret_cast<const f64x4 *>(m.opsA64);
     a.dt = m.scal + S_DT;
     a.bound = bound && !rhs && m.vmax ? 1 : 0;
     a.fgeo = m.fgeo64;
@@ -441,7 +607,16 @@ hipError_t launch_stage_mfma64(const DevMesh &m, const void *Uin, void *Uout, vo
         constexpr int P = decltype(PC)::value;
         using S = Tri64<P>;
         const int blocks = (m.K + S::EB - 1) / S::EB;
-        hipLaunchKernelGGL((k_stage_mfma64<P>), dim3(blocks), dim3(S::NTH), 0, st, a);
+        a.chunk = in_cache ? xcd_chunk(blocks) : 0;
+        const dim3 grid(xcd_grid(blocks)), block(S::NTH);
+        if (m.av) {
+            // (curved or not: one variant, the tile's test is cheap)
+            if constexpr (P >= kMinMatrix64) hipLaunchKernelGGL((k_stage_mfma64<P, true, true>), grid, block, 0, st, a);
+        } else if (m.Kc) {
+            if constexpr (P >= kMinMatrix64) hipLaunchKernelGGL((k_stage_mfma64<P, false, true>), grid, block, 0, st, a);
+        } else {
+            hipLaunchKernelGGL((k_stage_mfma64<P, false, false>), grid, block, 0, st, a);
+        }
         return hipGetLastError();
     });
 }
