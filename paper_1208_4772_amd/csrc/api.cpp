@@ -574,7 +574,8 @@ int dg_mesh_setup(const dg_mesh_desc *d, void *stream, dg_mesh **out) {
         dm.wgeoA64 = geoA_d;
         dm.wgeoF64 = geoF_d;
         dm.wgeoC64 = geoC_d;
-        dm.wminv64 = minv_d;
+        const double *fold_d = P == 1 ? minv_d : work_d;   // P = 1 runs on the VALUs with M_k^-1 itself
+        dm.wmfold64 = fold_d;
         if (dm.fp32) {
             float *o32, *a32, *f32, *c32, *m32;
             const size_t nC = size_t(Kc) * NQ * 4, nM = size_t(Kc) * Np * Np;
@@ -586,23 +587,30 @@ int dg_mesh_setup(const dg_mesh_desc *d, void *stream, dg_mesh **out) {
             SETUP_TRY(launch_cast(geoA_d, a32, size_t(K) * 5, st));
             SETUP_TRY(launch_cast(geoF_d, f32, size_t(K) * 3 * NG * 3, st));
             SETUP_TRY(launch_cast(geoC_d, c32, nC, st));
-            SETUP_TRY(launch_cast(minv_d, m32, nM, st));
+            SETUP_TRY(launch_cast(fold_d, m32, nM, st));
             dm.wops32 = o32;
             dm.wgeoA32 = a32;
             dm.wgeoF32 = f32;
             dm.wgeoC32 = c32;
-            dm.wminv32 = m32;
-            if (Kc == 0) {
-                // every element straight: the stage runs on the matrix cores
-                std::vector<float> fr(weak_mfma_opsA_values(P));
-                weak_mfma_fill_opsA(P, W.Icub.data(), W.Drc.data(), W.Dsc.data(), W.If.data(), W.Minv.data(),
-                                    fr.data());
-                float *fa;
-                if ((rc = m->alloc(&fa, fr.size()))) return cleanup(rc);
-                SETUP_TRY(hipMemcpyAsync(fa, fr.data(), sizeof(float) * fr.size(), hipMemcpyHostToDevice, st));
-                SETUP_TRY(hipStreamSynchronize(st));
-                dm.wopsA = fa;
-            }
+            dm.wmfold32 = m32;
+        }
+        // the stage's operator fragments in the handle's precision
+        const WeakOpsView view{W.Icub.data(), W.Drc.data(), W.Dsc.data(), W.If.data(), W.Minv.data()};
+        const size_t nF = weak_frag_values(P, dm.fp32);
+        std::vector<float> fr32(dm.fp32 ? nF : 0);
+        std::vector<double> fr64(dm.fp32 ? 0 : nF);
+        if (dm.fp32) {
+            float *f_d;
+            if ((rc = m->alloc(&f_d, nF))) return cleanup(rc);
+            weak_fill_frags(P, view, fr32.data());
+            SETUP_TRY(hipMemcpyAsync(f_d, fr32.data(), sizeof(float) * nF, hipMemcpyHostToDevice, st));
+            dm.wfrag32 = f_d;
+        } else {
+            double *f_d;
+            if ((rc = m->alloc(&f_d, nF))) return cleanup(rc);
+            weak_fill_frags(P, view, fr64.data());
+            SETUP_TRY(hipMemcpyAsync(f_d, fr64.data(), sizeof(double) * nF, hipMemcpyHostToDevice, st));
+            dm.wfrag64 = f_d;
         }
         SETUP_TRY(hipStreamSynchronize(st));
     }

@@ -33,14 +33,14 @@ struct DevMesh {
     bool weak = false;             // the over-integrated weak form instead of the nodal form
     // weak-form tables (weak.hip): operators Icub | Drc | Dsc | wq | If | Minv,
     // straight-element metrics [K][5], face data [K][3][NG][3], curved
-    // elements' mapped cubature weights [Kc][NQ][4] and inverse mass matrices
+    // elements' mapped cubature weights [Kc][NQ][4] and M_k^-1 M_ref (P = 1: M_k^-1)
     const double *wops64 = nullptr, *wgeoA64 = nullptr, *wgeoF64 = nullptr, *wgeoC64 = nullptr,
-                 *wminv64 = nullptr;
+                 *wmfold64 = nullptr;
     const float *wops32 = nullptr, *wgeoA32 = nullptr, *wgeoF32 = nullptr, *wgeoC32 = nullptr,
-                *wminv32 = nullptr;
+                *wmfold32 = nullptr;
     const int *widx = nullptr;     // [K] curved slot of the weak-form tables or -1
-    const float *wopsA = nullptr;  // FP32 handles of straight elements: the weak form's matrix-core
-                                   // operator fragments (weak_mfma.hip)
+    const float *wfrag32 = nullptr;    // the stage's matrix-core operator fragments
+    const double *wfrag64 = nullptr;
     int wKc = 0;
     double gamma = 1.4, cfl = 0.5;
     double qinf[4] = {1, 0, 0, 2.5};
@@ -223,12 +223,13 @@ hipError_t launch_weak_geometry(const DevMesh &m, const double *x, const double 
                                 double *mass, double *work, hipStream_t st);
 hipError_t launch_stage_weak(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs, int stage,
                              hipStream_t st);
-// the weak form on the matrix cores (weak_mfma.hip): FP32, every element straight
-size_t weak_mfma_opsA_values(int P);
-void weak_mfma_fill_opsA(int P, const double *Icub, const double *Drc, const double *Dsc, const double *If,
-                         const double *Minv, float *out);
-hipError_t launch_stage_weak_mfma(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs, int stage,
-                                  hipStream_t st);
+// the stage's operator fragments (host operators as in WeakOps)
+struct WeakOpsView {
+    const double *Icub, *Drc, *Dsc, *If, *Minv;
+};
+size_t weak_frag_values(int P, bool fp32);
+void weak_fill_frags(int P, const WeakOpsView &w, float *out);
+void weak_fill_frags(int P, const WeakOpsView &w, double *out);
 // p-refinement: U_to [K][4][np_to] = I (np_to x np_from, row-major, host) U_from
 constexpr int kProlongMax = 21 * 21;
 hipError_t launch_prolong(int K, int np_from, int np_to, const double *I, bool fp32, const void *Uf, void *Ut,

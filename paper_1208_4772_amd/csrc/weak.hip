@@ -11,18 +11,19 @@
 // Cholesky factorisation on a curved one).  The paper forms S_x and M_k^{-1}
 // per curved element (Section 4); here a curved element keeps its metric
 // terms per cubature point and its inverse mass matrix, a straight one five
-// numbers.  The contractions run on the VALUs in the handle's precision
+// numbers.  The contractions run on the matrix cores in the handle's precision
 // (FP64 or FP32); the setup (metric terms at cubature and face points, mass
 // matrices, Cholesky) runs in FP64 on the GPU.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
+#include <vector>
 
 #include "common.hpp"
 #include "launch.hpp"
 
 namespace dg {
 namespace {
-
-constexpr int kWBlock = 256;
 
 template <int P>
 struct WShape {
@@ -31,26 +32,71 @@ struct WShape {
     static constexpr int NQ = n * n, NG = n;
 };
 
-// Elements per block: LDS of U, the cubature fluxes (2 x 4 x NQ), the face
-// fluxes (4 x 3 NG) and the right-hand side vector within a budget per
-// precision.  Measured at P = 5 on 1M elements: FP32 runs fastest with small
-// blocks (36 KB: 11 elements per block at P = 5, four blocks per CU), FP64
-// with large ones (60 KB: its registers, not the LDS, cap the resident
-// waves).  The reference operators stay in global memory (caches): staged
-// in LDS they cost more resident blocks than the reads they save.
-constexpr int kWeakBudgetF32 = 36 * 1024, kWeakBudgetF64 = 60 * 1024;
-
+// ---- the stage --------------------------------------------------------------
+//
+// A wavefront owns a group of four elements, 16 columns (element, field) of
+// v_mfma_f32_16x16x4f32 / v_mfma_f64_16x16x4f64, from the state to the
+// update, without a block barrier and without LDS between the products:
+//   1. a tile of 16 cubature points: Icub . U;
+//   2. a lane then holds one field at four points, its quad the four fields:
+//      a 4 x 4 transpose within the quad (DPP) gives each lane one point's
+//      four fields, it forms that point's fluxes a = w_q J (r_x F + r_y G),
+//      b = w_q J (s_x F + s_y G), and transposes them back;
+//   3. these registers are the next product's operand as they stand: the
+//      accumulator rows a lane holds are taken as that product's k order,
+//      and the operator fragments are laid out to match;
+//   4. the update's product A2 . [a; b], A2 = M_ref^-1 [Drc^T | Dsc^T | -L]
+//      formed in FP64 on the host (straight elements: M_k = J M_ref).
+// The face Gauss points take the same steps after the volume: the element's
+// own trace and the neighbour's are two products (the neighbour's operand
+// gathered straight into registers), each lane forms one point's numerical
+// flux.  A curved element's result still wants M_k^-1 M_ref (formed at setup)
+// instead of 1 / J: Np x Np per element on the VALUs.
+//
+// The fragments are the same for every group: a block stages them in LDS and
+// its wavefronts walk several groups (read from the caches for every group
+// they were 25 to 32 KB of loads per four elements).  A large mesh is bound by
+// issue: an FP32 product takes its SIMD 32 cycles and the VALUs' work (fluxes,
+// transposes) adds to that, so 100,000 straight elements at P = 5 run a stage
+// in 100 us, 43% of it the products and 45% the VALUs (132 us with a block
+// barrier between the products and the fluxes in LDS).  A small one is bound
+// by the chain of a group's products: 5,000 elements at P = 4 in FP64 take 15
+// us a stage (22 us with the contractions on the VALUs, one element per
+// block).  Two steps of 100,000 elements, before and after: FP32 P = 4 1,878
+// and 875 us, FP64 P = 3 1,511 and 935 us, P = 5 4,579 and 2,190 us.  P = 1
+// has a kernel of its own below.
 template <typename T, int P>
-constexpr int weak_elems() {
-    using S = WShape<P>;
-    constexpr int per = (8 * S::Np + 8 * S::NQ + 12 * S::NG) * int(sizeof(T));
-    constexpr int e = (sizeof(T) == 4 ? kWeakBudgetF32 : kWeakBudgetF64) / per;
-    return e < 1 ? 1 : (e > 32 ? 32 : e);
-}
+struct WeakM {
+    static constexpr int Np = WShape<P>::Np, Nfp = P + 1, NF3 = 3 * Nfp;
+    static constexpr int NQ = WShape<P>::NQ, NG = WShape<P>::NG, NFG = 3 * NG;
+    static constexpr int KS1 = (Np + 3) / 4, MT1 = (NQ + 15) / 16;    // volume points
+    static constexpr int KSF = (NF3 + 3) / 4, MG = (NFG + 15) / 16;   // face Gauss points
+    static constexpr int MT2 = (Np + 15) / 16;                        // update
+    // row of accumulator slot r of 16-lane group kq (consecutive rows per
+    // group in FP32, interleaved by 4 in FP64)
+    static __host__ __device__ constexpr int row(int mt, int kq, int r) {
+        return 16 * mt + (sizeof(T) == 4 ? 4 * kq + r : kq + 4 * r);
+    }
+    // whether slot r of tile mt holds a row below n in any lane
+    static __host__ __device__ constexpr bool used(int mt, int r, int n) { return row(mt, 0, r) < n; }
+    static constexpr int count_used(int tiles, int n) {
+        int c = 0;
+        for (int mt = 0; mt < tiles; ++mt)
+            for (int r = 0; r < 4; ++r) c += used(mt, r, n) ? 1 : 0;
+        return c;
+    }
+    static constexpr int VF = 16 / int(sizeof(T));   // fragments per 16-byte vector
+    // fragments in the order the kernel takes them
+    static constexpr int NZ = MT1 * KS1 + 2 * MT2 * count_used(MT1, NQ) + MG * (KS1 + KSF) + MT2 * count_used(MG, NFG);
+    static constexpr int NZV = (NZ + VF - 1) / VF;
+    static constexpr int TS = 16 * Np + 4;           // LDS values of a group's tile
+    static constexpr int NV = (16 * Np / VF + 63) / 64;   // 16-byte vectors of a tile per lane
+};
 
 template <typename T>
 struct WeakArgs {
     int K, stage, mode, riemann;
+    int ngroups, per;   // groups of four elements, and of an XCD
     T g, ra, rb;
     FarField<T> ff;
     const T *__restrict__ Uin;
@@ -59,168 +105,497 @@ struct WeakArgs {
     T *__restrict__ rhs;
     const int *__restrict__ nbr;
     const int *__restrict__ finfo;
-    const T *__restrict__ ops;     // Icub | Drc | Dsc | wq | If | Minv
+    const T *__restrict__ ops;     // Icub | Drc | Dsc | wq | If | M_ref^-1
+    const T *__restrict__ frag;    // [NZV][64][VF] operator fragments
+    const T *__restrict__ wq;      // [NQ] cubature weights
     const T *__restrict__ geoA;    // [K][5] r_x s_x r_y s_y J (straight elements)
     const T *__restrict__ geoF;    // [K][3][NG][3] n_x n_y w_g sJ
     const T *__restrict__ geoC;    // [Kc][NQ][4] w_q J (r_x, s_x, r_y, s_y)
-    const T *__restrict__ minv;    // [Kc][Np][Np] inverse mass matrix
+    const T *__restrict__ mfold;   // [Kc][Np][Np] M_k^-1 M_ref (P = 1: M_k^-1)
     const int *__restrict__ widx;  // [K] curved slot or -1
     const double *__restrict__ dt;
 };
 
-template <typename T, int P>
-__global__ __launch_bounds__(kWBlock) void k_stage_weak(WeakArgs<T> a) {
-    using S = WShape<P>;
-    constexpr int Np = S::Np, Nfp = S::Nfp, NQ = S::NQ, NG = S::NG, EB = weak_elems<T, P>();
-    __shared__ T sU[EB][kFields][Np];
-    __shared__ T sA[EB][kFields][NQ];
-    __shared__ T sB[EB][kFields][NQ];
-    __shared__ T sS[EB][kFields][3 * NG];
-    __shared__ T sb[EB][kFields][Np];
-    const long k0 = (long)blockIdx.x * EB;
-    const int nel = (int)min((long)EB, (long)a.K - k0);
-    const int tid = threadIdx.x;
+__device__ __forceinline__ float quad_swap(float v, std::integral_constant<int, 1>) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xf, 0xf, true));   // lane ^ 1
+}
+__device__ __forceinline__ float quad_swap(float v, std::integral_constant<int, 2>) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xf, 0xf, true));   // lane ^ 2
+}
+template <int X>
+__device__ __forceinline__ double quad_swap(double v, std::integral_constant<int, X>) {
+    constexpr int ctrl = X == 1 ? 0xB1 : 0x4E;
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+// Transpose of the 4 x 4 block a quad holds (x[j] of lane i <-> x[i] of lane j).
+template <typename T>
+__device__ __forceinline__ void quad_transpose(T (&x)[4], bool b0, bool b1) {
+#pragma unroll
+    for (int p = 0; p < 4; p += 2) {
+        const T u = quad_swap(x[p], std::integral_constant<int, 1>()), v = quad_swap(x[p + 1], std::integral_constant<int, 1>());
+        x[p] = b0 ? v : x[p];
+        x[p + 1] = b0 ? x[p + 1] : u;
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const T u = quad_swap(x[p], std::integral_constant<int, 2>()), v = quad_swap(x[p + 2], std::integral_constant<int, 2>());
+        x[p] = b1 ? v : x[p];
+        x[p + 2] = b1 ? x[p + 2] : u;
+    }
+}
 
-    const T *Icub = a.ops, *Drc = Icub + NQ * Np, *Dsc = Drc + NQ * Np, *wq = Dsc + NQ * Np;
+template <typename T>
+struct WeakVec;
+template <>
+struct WeakVec<float> {
+    typedef f32x4 V4;
+    typedef f32x4 V;
+    typedef f32v16 VG;
+};
+template <>
+struct WeakVec<double> {
+    typedef f64x4 V4;
+    typedef f64x2 V;
+    typedef f64v16 VG;
+};
+__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f64x4 mfma16(double a, double b, f64x4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// Waves per SIMD: FP32 four (100,000 elements at P = 4, two steps, 886 us; 924
+// at five and 1,066 at six, which spill); FP64 three up to P = 3 (947 against
+// 1,018 us at two, P = 3), two above (5,000 at P = 4, 20 steps: 1.72 against
+// 2.10 ms at three).
+template <typename T, int P>
+constexpr int weak_waves() {
+    return sizeof(T) == 4 ? 4 : (P <= 3 ? 3 : 2);
+}
+
+// Blocks of W wavefronts a compute unit holds at once (LDS and registers).
+template <typename T, int P>
+constexpr int weak_blocks(int W) {
+    using S = WeakM<T, P>;
+    const int lds = (S::NZV * 64 * S::VF + W * 2 * S::TS) * int(sizeof(T));
+    const int by_lds = 160 * 1024 / lds, by_regs = 4 * weak_waves<T, P>() / W;
+    const int n = by_lds < by_regs ? by_lds : by_regs;
+    return n < 1 ? 1 : n;
+}
+
+template <typename T, int P, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(weak_waves<T, P>()))) void k_stage_weak(WeakArgs<T> a) {
+    using S = WeakM<T, P>;
+    using V4 = typename WeakVec<T>::V4;
+    using V = typename WeakVec<T>::V;
+    using VG = typename WeakVec<T>::VG;
+    constexpr int Np = S::Np, Nfp = S::Nfp, NF3 = S::NF3, NQ = S::NQ, NG = S::NG, NFG = S::NFG;
+    constexpr int KS1 = S::KS1, MT1 = S::MT1, KSF = S::KSF, MG = S::MG, MT2 = S::MT2, VF = S::VF, NZV = S::NZV;
+    constexpr int NV = S::NV, TS = S::TS, NTH = 64 * W;
+    __shared__ __attribute__((aligned(16))) V sA[NZV * 64];
+    __shared__ __attribute__((aligned(16))) T sT[W][2][TS];   // a wavefront's state tile and result tile
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int col = lane & 15, kq = lane >> 4, c = lane & 3, le = col >> 2;
+    const bool b0 = lane & 1, b1 = lane & 2;
+    {
+        const V *f = reinterpret_cast<const V *>(a.frag);
+#pragma unroll 4
+        for (int z = tid; z < NZV * 64; z += NTH) sA[z] = f[z];
+    }
+    const T dt = a.mode ? T(*a.dt) : T(0);
+    T wqv[MT1];
+#pragma unroll
+    for (int mt = 0; mt < MT1; ++mt) wqv[mt] = a.wq[min(S::row(mt, kq, c), NQ - 1)];
+    __syncthreads();
+    T *sU = sT[wave][0], *sR = sT[wave][1];
+
+    // XCD x (block b runs on XCD b % 8) walks the x-th contiguous eighth of the groups
+    const int g0 = int(blockIdx.x % 8) * a.per, gend = min(g0 + a.per, a.ngroups);
+    const int step = int(gridDim.x / 8) * W;
+#pragma unroll 1
+    for (int grp = g0 + int(blockIdx.x / 8) * W + wave; grp < gend; grp += step) {
+        const long k0 = (long)grp * 4;
+        const int nel = (int)min(4L, (long)a.K - k0);
+        const long base = k0 * kFields * Np;
+        const int nvec = nel * kFields * Np / VF;
+        // columns past the mesh's end repeat its last element and are not written out
+        const long k = k0 + min(le, nel - 1);
+
+        // ---- loads: connectivity and the tile first, then the neighbours'
+        // traces (a boundary face reads the element itself and ignores it)
+        const int info = a.finfo[k], cs = a.widx[k];
+        int nb[3];
+#pragma unroll
+        for (int f = 0; f < 3; ++f) nb[f] = a.nbr[k * 3 + f];
+        VG uv[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) uv[v] = reinterpret_cast<const VG *>(a.Uin + base)[min(lane + 64 * v, nvec - 1)];
+        T ga[5];
+#pragma unroll
+        for (int i = 0; i < 5; ++i) ga[i] = a.geoA[k * 5 + i];
+        T un[KSF];
+#pragma unroll
+        for (int ks = 0; ks < KSF; ++ks) {
+            const int q = min(4 * ks + kq, NF3 - 1), f = q / Nfp, j = q - f * Nfp;
+            const int kn = f == 0 ? nb[0] : (f == 1 ? nb[1] : nb[2]);
+            const int vp = face_node(P, face_nbr_face(info, f), Nfp - 1 - j);
+            un[ks] = a.Uin[((long)kn * kFields + c) * Np + vp];
+        }
+        const bool curved = __any(cs >= 0);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int z = lane + 64 * v;
+            if (z < nvec) {
+#pragma unroll
+                for (int i = 0; i < VF; ++i) sU[VF * z + i] = uv[v][i];
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const T *ucol = sU + ((int)(k - k0) * kFields + c) * Np;
+        T u[KS1];
+#pragma unroll
+        for (int ks = 0; ks < KS1; ++ks) {
+            const int j = 4 * ks + kq;
+            u[ks] = 4 * ks + 3 < Np || j < Np ? ucol[min(j, Np - 1)] : T(0);
+        }
+
+        const V4 zero = {T(0), T(0), T(0), T(0)};
+        V4 acc[MT2];
+#pragma unroll
+        for (int m = 0; m < MT2; ++m) acc[m] = zero;
+        // the update divides by J on a straight element (M_k = J M_ref): the
+        // volume weights leave J out and the face weights take 1 / J
+        const T iJ = cs >= 0 ? T(1) : T(1) / ga[4];
+        V cur;
+        // the fragments in order, a vector of VF at a time (z is a constant
+        // at every call)
+        auto frag = [&](int z) -> T {
+            if (z % VF == 0) cur = sA[z / VF * 64 + lane];
+            return cur[z % VF];
+        };
+        int z = 0;
+        // ---- volume: 16 cubature points at a time
+#pragma unroll
+        for (int mt = 0; mt < MT1; ++mt) {
+            V4 s;
+#pragma unroll
+            for (int ks = 0; ks < KS1; ++ks) s = mfma16(frag(z++), u[ks], ks ? s : zero);
+            T x[4] = {s[0], s[1], s[2], s[3]};
+            quad_transpose(x, b0, b1);
+            const int q = S::row(mt, kq, c);   // this lane's point
+            const T ir = rcp(x[0]);
+            const T vx = x[1] * ir, vy = x[2] * ir, p = pressure_ir(a.g, x, ir);
+            const T F[kFields] = {x[1], x[1] * vx + p, x[2] * vx, (x[3] + p) * vx};
+            const T G[kFields] = {x[2], x[1] * vy, x[2] * vy + p, (x[3] + p) * vy};
+            T w[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = wqv[mt] * ga[i];
+            if (curved && cs >= 0) {
+                const T *gq = a.geoC + ((long)cs * NQ + min(q, NQ - 1)) * 4;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[i] = gq[i];
+            }
+            T fa[4], fb[4];
+            const bool in = 16 * mt + 15 < NQ || q < NQ;
+#pragma unroll
+            for (int i = 0; i < kFields; ++i) {
+                fa[i] = in ? w[0] * F[i] + w[2] * G[i] : T(0);
+                fb[i] = in ? w[1] * F[i] + w[3] * G[i] : T(0);
+            }
+            quad_transpose(fa, b0, b1);
+            quad_transpose(fb, b0, b1);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (S::used(mt, r, NQ)) {
+#pragma unroll
+                    for (int m = 0; m < MT2; ++m) acc[m] = mfma16(frag(z++), fa[r], acc[m]);
+#pragma unroll
+                    for (int m = 0; m < MT2; ++m) acc[m] = mfma16(frag(z++), fb[r], acc[m]);
+                }
+        }
+        // ---- faces: 16 Gauss points at a time
+#pragma unroll
+        for (int ks = 0; ks < KSF; ++ks)
+            if (4 * ks + 3 >= NF3 && 4 * ks + kq >= NF3) un[ks] = T(0);
+#pragma unroll
+        for (int mt = 0; mt < MG; ++mt) {
+            V4 s, t;
+#pragma unroll
+            for (int ks = 0; ks < KS1; ++ks) s = mfma16(frag(z++), u[ks], ks ? s : zero);
+#pragma unroll
+            for (int ks = 0; ks < KSF; ++ks) t = mfma16(frag(z++), un[ks], ks ? t : zero);
+            T um[4] = {s[0], s[1], s[2], s[3]}, up[4] = {t[0], t[1], t[2], t[3]};
+            quad_transpose(um, b0, b1);
+            quad_transpose(up, b0, b1);
+            const int fg = min(S::row(mt, kq, c), NFG - 1), f = fg / NG;
+            const T *gf = a.geoF + (k * NFG + fg) * 3;
+            const T nx = gf[0], ny = gf[1], ws = gf[2] * iJ;
+            const int code = face_bc(info, f);
+            if (code != BC_INTERIOR) ghost_state(a.g, code, um, nx, ny, a.ff, up);
+            T fm[kFields], fp[kFields], lm, lp, star[kFields];
+            normal_flux(a.g, um, nx, ny, fm, lm);
+            if (a.riemann == RIEMANN_HLLC) {
+                hllc_jump(a.g, um, up, nx, ny, fp);
+#pragma unroll
+                for (int i = 0; i < kFields; ++i) star[i] = fm[i] - fp[i];
+            } else {
+                normal_flux(a.g, up, nx, ny, fp, lp);
+                const T lam = T(0.5) * (lm > lp ? lm : lp);
+#pragma unroll
+                for (int i = 0; i < kFields; ++i) star[i] = T(0.5) * (fm[i] + fp[i]) - lam * (up[i] - um[i]);
+            }
+            const bool in = 16 * mt + 15 < NFG || S::row(mt, kq, c) < NFG;
+            T fs[4];
+#pragma unroll
+            for (int i = 0; i < kFields; ++i) fs[i] = in ? ws * star[i] : T(0);
+            quad_transpose(fs, b0, b1);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (S::used(mt, r, NFG)) {
+#pragma unroll
+                    for (int m = 0; m < MT2; ++m) acc[m] = mfma16(frag(z++), fs[r], acc[m]);
+                }
+        }
+        // ---- the result into the group's tile, (element, field, node)
+#pragma unroll
+        for (int m = 0; m < MT2; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = S::row(m, kq, r);
+                if (i < Np) sR[col * Np + i] = acc[m][r];
+            }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (curved) {
+            // curved elements: one lane per node, the four fields together
+            constexpr int NT = (4 * Np + 63) / 64;
+            T val[NT][kFields];
+            bool mine[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const int task = lane + 64 * t, e = task / Np, i = task - e * Np;
+                const int ce = task < 4 * Np && e < nel ? a.widx[k0 + e] : -1;
+                mine[t] = ce >= 0;
+                if (mine[t]) {
+                    const T *M = a.mfold + (long)ce * Np * Np + i * Np;
+#pragma unroll
+                    for (int f = 0; f < kFields; ++f) val[t][f] = T(0);
+#pragma unroll 5
+                    for (int j = 0; j < Np; ++j) {
+                        const T m = M[j];
+#pragma unroll
+                        for (int f = 0; f < kFields; ++f) val[t][f] += m * sR[(e * kFields + f) * Np + j];
+                    }
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const int task = lane + 64 * t, e = task / Np, i = task - e * Np;
+                if (mine[t]) {
+#pragma unroll
+                    for (int f = 0; f < kFields; ++f) sR[(e * kFields + f) * Np + i] = val[t][f];
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        // ---- Runge-Kutta update (or the bare rhs), coalesced
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int zv = lane + 64 * v;
+            if (zv < nvec) {
+                VG rh, un4;
+#pragma unroll
+                for (int i = 0; i < VF; ++i) {
+                    rh[i] = sR[VF * zv + i];
+                    un4[i] = sU[VF * zv + i];
+                }
+                if (a.mode == 0) {
+                    reinterpret_cast<VG *>(a.rhs + base)[zv] = rh;
+                } else {
+                    VG rr = dt * rh;
+                    if (a.stage > 0) rr = a.ra * reinterpret_cast<const VG *>(a.R + base)[zv] + dt * rh;
+                    reinterpret_cast<VG *>(a.R + base)[zv] = rr;
+                    reinterpret_cast<VG *>(a.Uout + base)[zv] = un4 + a.rb * rr;
+                }
+            }
+        }
+        // the tiles are reused by the next group
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// P = 1 on the VALUs: three nodes and four cubature points fill too little of
+// a 16-row tile (100,000 straight elements, 20 steps: 1.62 ms here and 2.75 on
+// the tiles above in FP32, 2.53 and 3.72 in FP64).  A block takes 32 elements,
+// a thread one point: wavefronts 0 to 2 the 192 face Gauss points, 2 and 3 the
+// 128 cubature points, both straight from global memory; after the only
+// barrier a quad of wavefronts 0 and 1 takes an element's three nodes.  Bound
+// by the chain connectivity, neighbour's trace, flux, update, so every load is
+// issued as early as its address is known; blocks walk the mesh contiguously
+// per XCD, so that the traces stay in its L2 (500,000 elements, four steps:
+// 1.72 -> 1.25 ms in FP32, 2.65 -> 2.33 in FP64 against a kernel with the
+// state in LDS and three barriers).  A bound on the registers for a fourth
+// FP64 wavefront per SIMD spills: 3.72 ms.  mfold holds M_k^-1 itself here.
+constexpr int kW1Elems = 32, kW1Block = 256;
+
+template <typename T>
+__global__ __launch_bounds__(kW1Block) void k_stage_weak1(WeakArgs<T> a) {
+    using S = WShape<1>;
+    constexpr int Np = S::Np, Nfp = S::Nfp, NQ = S::NQ, NG = S::NG, EB = kW1Elems, NFP = EB * 3 * NG;
+    static_assert(NQ == 4 && NFP % 64 == 0 && EB * NQ % 64 == 0 && EB * 4 <= kW1Block, "thread roles");
+    __shared__ T sA[EB][kFields * 2 * NQ + 4];   // + 4: elements on different banks
+    __shared__ T sS[EB][kFields * 3 * NG + 4];
+    const int tile = xcd_tile(a.per), tid = threadIdx.x;
+    if (tile >= a.ngroups) return;
+    const long k0 = (long)tile * EB;
+    const int nel = (int)min((long)EB, (long)a.K - k0);
+    const T *Icub = a.ops, *Drc = Icub + NQ * Np, *wq = Drc + 2 * NQ * Np;
     const T *If = wq + NQ, *Minv = If + NG * Nfp;
 
-    for (int z = tid; z < nel * kFields * Np; z += kWBlock) (&sU[0][0][0])[z] = a.Uin[k0 * kFields * Np + z];
-    __syncthreads();
-
-    // volume fluxes at the cubature points, weighted and mapped
-    for (int z = tid; z < nel * NQ; z += kWBlock) {
-        const int el = z / NQ, q = z - el * NQ;
-        const long k = k0 + el;
+    // Loads in the order they are wanted, no use of one before the last is
+    // issued: connectivity, the update's operands, then the traces of a face
+    // Gauss point, the neighbour's at the address the connectivity gave.
+    const bool face = tid < NFP;
+    const int el = min(tid / (3 * NG), EB - 1), fg = tid % (3 * NG), f = fg / NG, gq = fg - f * NG;
+    const long k = k0 + min(el, nel - 1);
+    T u0[kFields], u1[kFields], v0[kFields], v1[kFields], gf[3], l0, l1;
+    int info = 0, kb = 0;
+    if (face) {
+        info = a.finfo[k];
+        kb = a.nbr[k * 3 + f];
+        l0 = If[gq * Nfp];
+        l1 = If[gq * Nfp + 1];
+#pragma unroll
+        for (int m = 0; m < 3; ++m) gf[m] = a.geoF[((k * 3 + f) * NG + gq) * 3 + m];
+#pragma unroll
+        for (int c = 0; c < kFields; ++c) {
+            u0[c] = a.Uin[(k * kFields + c) * Np + face_node(1, f, 0)];
+            u1[c] = a.Uin[(k * kFields + c) * Np + face_node(1, f, 1)];
+        }
+    }
+    // the update's operands (threads below 128: node i of element ne)
+    const int ne = tid >> 2, i = tid & 3;
+    const bool node = ne < nel && i < Np;
+    const long at = (k0 + ne) * kFields * Np + i;
+    T un[kFields], rn[kFields], dn[2 * NQ], ln[3][NG], mn[Np], J = T(1);
+    const T dt = a.mode ? T(*a.dt) : T(0);
+    int cs = -1;
+    if (node) {
+        cs = a.widx[k0 + ne];
+        J = a.geoA[(k0 + ne) * 5 + 4];
+#pragma unroll
+        for (int c = 0; c < kFields; ++c) {
+            un[c] = a.Uin[at + c * Np];
+            rn[c] = a.stage > 0 ? a.R[at + c * Np] : T(0);
+        }
+#pragma unroll
+        for (int q = 0; q < 2 * NQ; ++q) dn[q] = Drc[q * Np + i];
+#pragma unroll
+        for (int ff = 0; ff < 3; ++ff)
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const int j = i == face_node(1, ff, 0) ? 0 : 1;
+                ln[ff][g] = If[g * Nfp + j];
+            }
+#pragma unroll
+        for (int j = 0; j < Np; ++j) mn[j] = Minv[i * Np + j];
+    }
+    if (face) {
+        const int fn = face_nbr_face(info, f);   // the neighbour's face runs backwards
+#pragma unroll
+        for (int c = 0; c < kFields; ++c) {
+            v0[c] = a.Uin[((long)kb * kFields + c) * Np + face_node(1, fn, 1)];
+            v1[c] = a.Uin[((long)kb * kFields + c) * Np + face_node(1, fn, 0)];
+        }
+    }
+    if (tid >= kW1Block - EB * NQ) {
+        // volume fluxes at a cubature point, weighted and mapped
+        const int z = tid - (kW1Block - EB * NQ), eq = z / NQ, q = z % NQ;
+        const long kq = k0 + min(eq, nel - 1);
+        const int cq = a.widx[kq];
+        const T *U = a.Uin + kq * kFields * Np;
+        const T wJ = wq[q] * a.geoA[kq * 5 + 4];
+        T gm[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) gm[m] = wJ * a.geoA[kq * 5 + m];
         T u[kFields] = {};
+#pragma unroll
         for (int j = 0; j < Np; ++j) {
             const T phi = Icub[q * Np + j];
 #pragma unroll
-            for (int c = 0; c < kFields; ++c) u[c] += phi * sU[el][c][j];
+            for (int c = 0; c < kFields; ++c) u[c] += phi * U[c * Np + j];
         }
+        if (cq >= 0)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) gm[m] = a.geoC[((long)cq * NQ + q) * 4 + m];
         const T ir = rcp(u[0]);
         const T vx = u[1] * ir, vy = u[2] * ir, p = pressure_ir(a.g, u, ir);
         const T F[kFields] = {u[1], u[1] * vx + p, u[2] * vx, (u[3] + p) * vx};
         const T G[kFields] = {u[2], u[1] * vy, u[2] * vy + p, (u[3] + p) * vy};
-        const int cs = a.widx[k];
-        T wrx, wsx, wry, wsy;
-        if (cs < 0) {
-            const T *gk = a.geoA + k * 5;
-            const T wJ = wq[q] * gk[4];
-            wrx = wJ * gk[0];
-            wsx = wJ * gk[1];
-            wry = wJ * gk[2];
-            wsy = wJ * gk[3];
-        } else {
-            const T *gq = a.geoC + ((long)cs * NQ + q) * 4;
-            wrx = gq[0];
-            wsx = gq[1];
-            wry = gq[2];
-            wsy = gq[3];
-        }
 #pragma unroll
         for (int c = 0; c < kFields; ++c) {
-            sA[el][c][q] = wrx * F[c] + wry * G[c];
-            sB[el][c][q] = wsx * F[c] + wsy * G[c];
+            sA[eq][c * 2 * NQ + q] = gm[0] * F[c] + gm[2] * G[c];
+            sA[eq][c * 2 * NQ + NQ + q] = gm[1] * F[c] + gm[3] * G[c];
         }
     }
-    // numerical fluxes at the face Gauss points, times w_g sJ
-    for (int z = tid; z < nel * 3 * NG; z += kWBlock) {
-        const int el = z / (3 * NG), fg = z - el * 3 * NG, f = fg / NG, gq = fg - f * NG;
-        const long k = k0 + el;
-        T um[kFields] = {}, up[kFields] = {};
-        for (int j = 0; j < Nfp; ++j) {
-            const T l = If[gq * Nfp + j];
-            const int v = face_node(P, f, j);
-#pragma unroll
-            for (int c = 0; c < kFields; ++c) um[c] += l * sU[el][c][v];
-        }
-        const T *gf = a.geoF + ((k * 3 + f) * NG + gq) * 3;
+
+    if (face) {
+        // numerical flux at the face Gauss point, times w_g sJ
         const T nx = gf[0], ny = gf[1], ws = gf[2];
-        const int info = a.finfo[k];
-        const int code = face_bc(info, f);
-        if (code == BC_INTERIOR) {
-            // the neighbour's face node Nfp-1-j sits on this face's node j
-            const long kn = a.nbr[k * 3 + f];
-            const int fn = face_nbr_face(info, f);
-            for (int j = 0; j < Nfp; ++j) {
-                const T l = If[gq * Nfp + j];
-                const int v = face_node(P, fn, Nfp - 1 - j);
+        T um[kFields], up[kFields], fm[kFields], lm, d[kFields];
 #pragma unroll
-                for (int c = 0; c < kFields; ++c) up[c] += l * a.Uin[(kn * kFields + c) * Np + v];
-            }
-        } else {
-            ghost_state(a.g, code, um, nx, ny, a.ff, up);
+        for (int c = 0; c < kFields; ++c) {
+            um[c] = l0 * u0[c] + l1 * u1[c];
+            up[c] = l0 * v0[c] + l1 * v1[c];
         }
-        T fm[kFields], lm, d[kFields];
+        const int code = face_bc(info, f);
+        if (code != BC_INTERIOR) ghost_state(a.g, code, um, nx, ny, a.ff, up);
         normal_flux(a.g, um, nx, ny, fm, lm);
         flux_jump(a.riemann, a.g, um, up, nx, ny, d);
 #pragma unroll
-        for (int c = 0; c < kFields; ++c) sS[el][c][fg] = ws * (fm[c] - d[c]);
+        for (int c = 0; c < kFields; ++c) sS[el][c * 3 * NG + fg] = ws * (fm[c] - d[c]);
+    }
+    if (cs >= 0) {
+        J = T(1);
+#pragma unroll
+        for (int j = 0; j < Np; ++j) mn[j] = a.mfold[((long)cs * Np + i) * Np + j];
     }
     __syncthreads();
-    // V - S per node, the four fields together (each operator entry read
-    // once for all of them)
-    constexpr NodeFaceTable<P> kNF;
-    for (int z = tid; z < nel * Np; z += kWBlock) {
-        const int el = z / Np, i = z - el * Np;
-        T b[kFields] = {};
-        for (int q = 0; q < NQ; ++q) {
-            const T dr = Drc[q * Np + i], ds = Dsc[q * Np + i];
+    if (ne >= EB) return;
+    // V - S at the node, M_k^-1 over the quad, the Runge-Kutta update
 #pragma unroll
-            for (int c = 0; c < kFields; ++c) b[c] += dr * sA[el][c][q] + ds * sB[el][c][q];
+    for (int c = 0; c < kFields; ++c) {
+        T b = T(0);
+        if (node) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) b += dn[q] * sA[ne][c * 2 * NQ + q] + dn[NQ + q] * sA[ne][c * 2 * NQ + NQ + q];
+#pragma unroll
+            for (int f = 0; f < 3; ++f)
+#pragma unroll
+                for (int g = 0; g < NG; ++g) b -= (i == face_node(1, f, 0) || i == face_node(1, f, 1) ? ln[f][g] : T(0)) * sS[ne][(c * 3 + f) * NG + g];
         }
-        const int nq = kNF.v[i];
-        if (nq) {
-            for (int t = 0; t < 2; ++t) {
-                const int e = t == 0 ? (nq & 255) - 1 : (nq >> 8) - 1;
-                if (e < 0) continue;
-                const int f = e / Nfp, j = e - f * Nfp;
-                for (int gq = 0; gq < NG; ++gq) {
-                    const T l = If[gq * Nfp + j];
+        T val = T(0);
 #pragma unroll
-                    for (int c = 0; c < kFields; ++c) b[c] -= l * sS[el][c][f * NG + gq];
-                }
-            }
+        for (int j = 0; j < Np; ++j) {
+            const T bj = __shfl(b, j, 4);
+            if (node) val += mn[j] * bj;
         }
-#pragma unroll
-        for (int c = 0; c < kFields; ++c) sb[el][c][i] = b[c];
-    }
-    __syncthreads();
-    // M_k^{-1} (V - S), then the Runge-Kutta update, the four fields of a
-    // node together
-    const T dt = a.mode ? T(*a.dt) : T(0);
-    for (int z = tid; z < nel * Np; z += kWBlock) {
-        const int el = z / Np, i = z - el * Np;
-        const long k = k0 + el;
-        const int cs = a.widx[k];
-        T val[kFields] = {};
-        if (cs < 0) {
-            for (int j = 0; j < Np; ++j) {
-                const T mij = Minv[i * Np + j];
-#pragma unroll
-                for (int c = 0; c < kFields; ++c) val[c] += mij * sb[el][c][j];
-            }
-            const T J = a.geoA[k * 5 + 4];
-#pragma unroll
-            for (int c = 0; c < kFields; ++c) val[c] = val[c] / J;
+        if (!node) continue;
+        val = val / J;
+        if (a.mode == 0) {
+            a.rhs[at + c * Np] = val;
         } else {
-            const T *mk = a.minv + (long)cs * Np * Np + i * Np;
-            for (int j = 0; j < Np; ++j) {
-                const T mij = mk[j];
-#pragma unroll
-                for (int c = 0; c < kFields; ++c) val[c] += mij * sb[el][c][j];
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < kFields; ++c) {
-            const long idx = k0 * kFields * Np + (el * kFields + c) * Np + i;
-            if (a.mode == 0) {
-                a.rhs[idx] = val[c];
-            } else {
-                const T rr = (a.stage == 0) ? dt * val[c] : a.ra * a.R[idx] + dt * val[c];
-                a.R[idx] = rr;
-                a.Uout[idx] = sU[el][c][i] + a.rb * rr;
-            }
+            const T rr = a.stage == 0 ? dt * val : a.ra * rn[c] + dt * val;
+            a.R[at + c * Np] = rr;
+            a.Uout[at + c * Np] = un[c] + a.rb * rr;
         }
     }
 }
@@ -351,6 +726,18 @@ __global__ void k_weak_minv(int Kc, int Np, double *__restrict__ mass, double *_
     }
 }
 
+// M_k^-1 M_ref of each curved element (the update's fragments carry M_ref^-1).
+__global__ void k_weak_fold(int Kc, int Np, const double *__restrict__ minv, const double *__restrict__ Mref,
+                            double *__restrict__ out) {
+    const long g = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= (long)Kc * Np * Np) return;
+    const int j = int(g % Np);
+    const double *row = minv + g / Np * Np;
+    double v = 0.0;
+    for (int m = 0; m < Np; ++m) v += row[m] * Mref[m * Np + j];
+    out[g] = v;
+}
+
 template <typename F>
 hipError_t with_order_w(int P, F &&f) {
     switch (P) {
@@ -360,6 +747,74 @@ hipError_t with_order_w(int P, F &&f) {
         case 4: return f(std::integral_constant<int, 4>());
         case 5: return f(std::integral_constant<int, 5>());
         default: return hipErrorInvalidValue;
+    }
+}
+
+// Operator fragments in the order the kernel takes them: lane l holds row
+// l % 16 of the 16-row tile and the k-step's column of its 16-lane group.
+template <typename T, int P>
+void fill_weak_frags(const double *Icub, const double *Drc, const double *Dsc, const double *If, const double *Minv,
+                     T *out) {
+    using S = WeakM<T, P>;
+    constexpr int Np = S::Np, Nfp = S::Nfp, NQ = S::NQ, NG = S::NG, NFG = S::NFG, K2 = 2 * NQ + NFG;
+    std::vector<double> B(size_t(Np) * K2, 0.0), A2(size_t(Np) * K2, 0.0);
+    for (int i = 0; i < Np; ++i)
+        for (int q = 0; q < NQ; ++q) {
+            B[size_t(i) * K2 + q] = Drc[q * Np + i];
+            B[size_t(i) * K2 + NQ + q] = Dsc[q * Np + i];
+        }
+    for (int f = 0; f < 3; ++f)
+        for (int j = 0; j < Nfp; ++j)
+            for (int g = 0; g < NG; ++g) B[size_t(face_node(P, f, j)) * K2 + 2 * NQ + f * NG + g] = -If[g * Nfp + j];
+    for (int i = 0; i < Np; ++i)
+        for (int k = 0; k < K2; ++k) {
+            double s = 0.0;
+            for (int m = 0; m < Np; ++m) s += Minv[i * Np + m] * B[size_t(m) * K2 + k];
+            A2[size_t(i) * K2 + k] = s;
+        }
+    for (int z = 0; z < S::NZV * 64 * S::VF; ++z) out[z] = T(0);
+    int z = 0;
+    // one fragment: value(row within the operator, 16-lane group)
+    auto put = [&](int mt, auto &&value) {
+        for (int l = 0; l < 64; ++l) out[(z / S::VF * 64 + l) * S::VF + z % S::VF] = T(value(16 * mt + (l & 15), l >> 4));
+        ++z;
+    };
+    auto update = [&](int n, int first, int mt, int r) {   // A2's columns first + row(mt, kq, r)
+        for (int m = 0; m < S::MT2; ++m)
+            put(m, [&](int i, int kq) {
+                const int col = S::row(mt, kq, r);
+                return i < Np && col < n ? A2[size_t(i) * K2 + first + col] : 0.0;
+            });
+    };
+    for (int mt = 0; mt < S::MT1; ++mt) {
+        for (int ks = 0; ks < S::KS1; ++ks)
+            put(mt, [&](int q, int kq) {
+                const int j = 4 * ks + kq;
+                return q < NQ && j < Np ? Icub[q * Np + j] : 0.0;
+            });
+        for (int r = 0; r < 4; ++r)
+            if (S::used(mt, r, NQ)) {
+                update(NQ, 0, mt, r);
+                update(NQ, NQ, mt, r);
+            }
+    }
+    for (int mt = 0; mt < S::MG; ++mt) {
+        for (int ks = 0; ks < S::KS1; ++ks)   // the element's own trace
+            put(mt, [&](int fg, int kq) {
+                const int node = 4 * ks + kq;
+                double v = 0.0;
+                if (fg < NFG && node < Np)
+                    for (int j = 0; j < Nfp; ++j)
+                        if (face_node(P, fg / NG, j) == node) v = If[(fg % NG) * Nfp + j];
+                return v;
+            });
+        for (int ks = 0; ks < S::KSF; ++ks)   // the neighbour's, at this element's face nodes
+            put(mt, [&](int fg, int kq) {
+                const int q = 4 * ks + kq;
+                return fg < NFG && q < S::NF3 && q / Nfp == fg / NG ? If[(fg % NG) * Nfp + q % Nfp] : 0.0;
+            });
+        for (int r = 0; r < 4; ++r)
+            if (S::used(mt, r, NFG)) update(NFG, 2 * NQ, mt, r);
     }
 }
 
@@ -383,29 +838,82 @@ hipError_t stage_weak_t(const DevMesh &m, const void *Uin, void *Uout, void *R, 
     a.finfo = m.finfo;
     if constexpr (sizeof(T) == 8) {
         a.ops = m.wops64;
+        a.frag = m.wfrag64;
         a.geoA = m.wgeoA64;
         a.geoF = m.wgeoF64;
         a.geoC = m.wgeoC64;
-        a.minv = m.wminv64;
+        a.mfold = m.wmfold64;
     } else {
         a.ops = m.wops32;
+        a.frag = m.wfrag32;
         a.geoA = m.wgeoA32;
         a.geoF = m.wgeoF32;
         a.geoC = m.wgeoC32;
-        a.minv = m.wminv32;
+        a.mfold = m.wmfold32;
     }
     a.widx = m.widx;
     a.dt = m.scal + S_DT;
+    a.ngroups = (m.K + 3) / 4;
+    a.per = (a.ngroups + 7) / 8;
     return with_order_w(m.P, [&](auto PC) {
         constexpr int P = decltype(PC)::value;
-        constexpr int EB = weak_elems<T, P>();
-        const dim3 grid(unsigned((m.K + EB - 1) / EB)), block(kWBlock);
-        hipLaunchKernelGGL((k_stage_weak<T, P>), grid, block, 0, st, a);
-        return hipGetLastError();
+        using S = WeakM<T, P>;
+        a.wq = a.ops + size_t(3) * S::NQ * S::Np;
+        if constexpr (P == 1) {
+            a.ngroups = (m.K + kW1Elems - 1) / kW1Elems;
+            a.per = xcd_chunk(a.ngroups);
+            hipLaunchKernelGGL((k_stage_weak1<T>), dim3(xcd_grid(a.ngroups)), dim3(kW1Block), 0, st, a);
+            return hipGetLastError();
+        } else {
+            // Wavefronts that share a block's fragments: four, or eight where
+            // only that lets the LDS hold as many wavefronts as the registers
+            // do (P = 5: 100,000 FP32 elements, two steps, 2,112 against 2,156
+            // us; 20,000 FP64, four steps, 1,109 against 1,231 us) and every
+            // SIMD has a group.  Elsewhere four: less padding in a small
+            // mesh's last block (800 FP32 elements at P = 3, 60 steps, 2,163
+            // against 2,374 us; 20,000 at P = 2, 20 steps, 1,047 against 1,106
+            // us).
+            constexpr int w4 = 4 * weak_blocks<T, P>(4), w8 = 8 * weak_blocks<T, P>(8);
+            auto go = [&](auto WC) {
+                constexpr int W = decltype(WC)::value;
+                const int want = 8 * ((a.per + W - 1) / W), most = 256 * weak_blocks<T, P>(W);
+                hipLaunchKernelGGL((k_stage_weak<T, P, W>), dim3(unsigned(want < most ? want : most)), dim3(64 * W), 0, st, a);
+            };
+            if constexpr (w8 > w4) {
+                if (a.ngroups > 256 * 4) {
+                    go(std::integral_constant<int, 8>());
+                    return hipGetLastError();
+                }
+            }
+            go(std::integral_constant<int, 4>());
+            return hipGetLastError();
+        }
     });
 }
 
 }  // namespace
+
+size_t weak_frag_values(int P, bool fp32) {
+    size_t n = 0;
+    (void)with_order_w(P, [&](auto PC) {
+        constexpr int PP = decltype(PC)::value;
+        n = size_t(64) * (fp32 ? WeakM<float, PP>::NZV * 4 : WeakM<double, PP>::NZV * 2);
+        return hipSuccess;
+    });
+    return n;
+}
+
+template <typename T>
+static void fill_frags(int P, const WeakOpsView &w, T *out) {
+    (void)with_order_w(P, [&](auto PC) {
+        constexpr int PP = decltype(PC)::value;
+        fill_weak_frags<T, PP>(w.Icub, w.Drc, w.Dsc, w.If, w.Minv, out);
+        return hipSuccess;
+    });
+}
+
+void weak_fill_frags(int P, const WeakOpsView &w, float *out) { fill_frags(P, w, out); }
+void weak_fill_frags(int P, const WeakOpsView &w, double *out) { fill_frags(P, w, out); }
 
 size_t weak_ops_size(int P) {
     const int Np = (P + 1) * (P + 2) / 2, Nfp = P + 1, n = (3 * P + 2) / 2, NQ = n * n;
@@ -424,12 +932,15 @@ hipError_t launch_weak_geometry(const DevMesh &m, const double *x, const double 
     if (e != hipSuccess || m.wKc == 0) return e;
     hipLaunchKernelGGL(k_weak_minv, dim3((m.wKc + 63) / 64), dim3(64), 0, st, m.wKc, m.Np, mass, work,
                        m.count + 2);
+    // the factorisation is done with: the folded matrices take its place
+    const long n = (long)m.wKc * m.Np * m.Np;
+    hipLaunchKernelGGL(k_weak_fold, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, m.wKc, m.Np, mass,
+                       m.ops64 + ops_size(m.Np, m.Nfp), work);
     return hipGetLastError();
 }
 
 hipError_t launch_stage_weak(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs, int stage,
                              hipStream_t st) {
-    if (m.fp32 && m.wopsA) return launch_stage_weak_mfma(m, Uin, Uout, R, rhs, stage, st);
     return m.fp32 ? stage_weak_t<float>(m, Uin, Uout, R, rhs, stage, st)
                   : stage_weak_t<double>(m, Uin, Uout, R, rhs, stage, st);
 }
