@@ -514,6 +514,11 @@ int dg_mesh_setup(const dg_mesh_desc *d, void *stream, dg_mesh **out) {
         SETUP_TRY(hipStreamSynchronize(st));
     }
     if (dm.weak) {
+        if (!dm.vmax) {   // slots of the time-step bound, as above
+            unsigned long long *vmaxw_d;
+            if ((rc = m->alloc(&vmaxw_d, 2 * kVmaxSlots))) return cleanup(rc);
+            dm.vmax = vmaxw_d;
+        }
         // over-integrated weak form: cubature operators and the per-element
         // tables, computed in FP64 on the device; curved elements are those
         // whose nodal metric terms are not constant
@@ -705,11 +710,11 @@ int dg_rhs(dg_mesh *m, const void *U, void *rhs, double t, void *stream) {
 // One step: dt reduction on the device, then five stages ping-ponging
 // U -> A -> B -> A -> B -> U so that no stage writes the buffer whose face
 // traces other workgroups are still reading.
-// One step of a run of an FP64 handle on the FP64 matrix cores: dt from
-// the bound the previous step's last stage (or the run's first bound) left
+// One step of a run of an FP64 handle on the FP64 matrix cores or of a
+// weak-form handle: dt from the bound the previous step's last stage (or the run's first bound) left
 // in the slots, then the five stages, the last of which reduces the next
 // bound.  The same sums as launch_cfl and the stages, so the same bits.
-static int step_fused64(dg_mesh *m, void *U, void *work, double dt, hipStream_t st) {
+static int step_fused64(dg_mesh *m, void *U, void *work, double dt, hipStream_t st, bool closing) {
     char *w = static_cast<char *>(work);
     void *R = w + m->off_R();
     void *A = w + m->off_A();
@@ -719,14 +724,18 @@ static int step_fused64(dg_mesh *m, void *U, void *work, double dt, hipStream_t 
     HIP_TRY(launch_dt_slots64(m->dm, dt, st));
     for (int s = 0; s < 5; ++s) {
         HIP_TRY(m->time_begin(st));
-        HIP_TRY(launch_stage_mfma64(m->dm, in[s], out[s], R, nullptr, s, s == 4, nullptr, st));
+        if (m->dm.weak)
+            HIP_TRY(launch_stage_weak(m->dm, in[s], out[s], R, nullptr, s, s == 4 && !closing, st));
+        else
+            HIP_TRY(launch_stage_mfma64(m->dm, in[s], out[s], R, nullptr, s, s == 4, nullptr, st));
         HIP_TRY(m->time_end(st));
     }
     return DG_OK;
 }
 
-static int step_impl(dg_mesh *m, void *U, void *work, double dt, hipStream_t st, int fused_parity = -1) {
-    if (fused_parity >= 0 && !m->dm.fp32) return step_fused64(m, U, work, dt, st);
+static int step_impl(dg_mesh *m, void *U, void *work, double dt, hipStream_t st, int fused_parity = -1,
+                     bool closing = false) {
+    if (fused_parity >= 0 && (!m->dm.fp32 || m->dm.weak)) return step_fused64(m, U, work, dt, st, closing);
     char *w = static_cast<char *>(work);
     void *R = w + m->off_R();
     void *A = w + m->off_A();
@@ -918,9 +927,11 @@ int dg_run(dg_mesh *m, void *U, void *work, int nsteps, dg_run_stats *stats, voi
     HIP_TRY(hipEventRecord(e0, st));
     // fused runs: the bound of each step's state comes from the previous
     // step's last stage (FP32 matrix-core handles; FP64 handles on the FP64
-    // matrix cores, which have no viscosity)
-    const bool fused64 = !m->dm.fp32 && m->dm.opsA64 && !m->dm.av && !m->dm.weak;
-    const bool fused = (m->dm.fp32 && !m->dm.weak) || fused64;
+    // matrix cores without viscosity; weak-form handles, whose last step
+    // leaves no bound: their final state is not checked)
+    const bool weak = m->dm.weak;
+    const bool fused64 = !m->dm.fp32 && m->dm.opsA64 && !m->dm.av;
+    const bool fused = weak ? nsteps > 1 : (m->dm.fp32 || fused64);
     if (fused && nsteps > 0) {
         if (m->dm.av)
             HIP_TRY(hipMemsetAsync(m->dm.vmax, 0, 2 * kVmaxSlots * sizeof(unsigned long long), st));
@@ -928,12 +939,12 @@ int dg_run(dg_mesh *m, void *U, void *work, int nsteps, dg_run_stats *stats, voi
             HIP_TRY(launch_cfl_vmax(m->dm, U, m->dm.vmax, st));
     }
     int done = 0;
-    if (fused && m->graphs && !m->timing && nsteps >= 2) {
+    if (fused && !weak && m->graphs && !m->timing && nsteps >= 2) {
         if (int rc = ensure_step_graph(m, U, work)) return rc;
         for (; done + 2 <= nsteps; done += 2) HIP_TRY(hipGraphLaunch(m->graph_exec, st));
     }
     for (int n = done; n < nsteps; ++n) {
-        if (int rc = step_impl(m, U, work, 0.0, st, fused ? (n & 1) : -1)) {
+        if (int rc = step_impl(m, U, work, 0.0, st, fused ? (n & 1) : -1, weak && n == nsteps - 1)) {
             (void)hipEventDestroy(e0);
             (void)hipEventDestroy(e1);
             return rc;

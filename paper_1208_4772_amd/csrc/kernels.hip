@@ -1258,7 +1258,7 @@ hipError_t launch_stage(const DevMesh &m, const void *Uin, void *Uout, void *R, 
     // the weak form: its own kernel; FP32 (with or without viscosity): the
     // matrix-core kernel; FP64: the FP64 matrix cores where use_mfma64 says
     // so, else VALU
-    if (m.weak) return launch_stage_weak(m, Uin, Uout, R, rhs, stage, st);
+    if (m.weak) return launch_stage_weak(m, Uin, Uout, R, rhs, stage, false, st);
     if (m.fp32) return launch_stage_mfma(m, Uin, Uout, R, rhs, stage, MfmaStep(), st, Q);
     if (m.opsA64) return launch_stage_mfma64(m, Uin, Uout, R, rhs, stage, false, Q, st);
     return stage_t<double>(m, Uin, Uout, R, rhs, stage, Q, st);
@@ -1418,7 +1418,7 @@ static hipError_t cfl_t(const DevMesh &m, const void *U, const void *eps, double
 }
 
 hipError_t launch_cfl_vmax(const DevMesh &m, const void *U, unsigned long long *slot, hipStream_t st) {
-    if (m.fp32) return launch_cfl_vmax_mfma(m, U, slot, st);
+    if (m.fp32 && !m.weak) return launch_cfl_vmax_mfma(m, U, slot, st);
     hipError_t e = with_order(m.P, [&](auto PC) {
         constexpr int P = decltype(PC)::value;
         if (m.fp32)

@@ -222,7 +222,7 @@ hipError_t launch_weak_geometry(const DevMesh &m, const double *x, const double 
                                 const double *Dsg, const double *wg, double *geoA, double *geoF, double *geoC,
                                 double *mass, double *work, hipStream_t st);
 hipError_t launch_stage_weak(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs, int stage,
-                             hipStream_t st);
+                             bool bound, hipStream_t st);
 // the stage's operator fragments (host operators as in WeakOps)
 struct WeakOpsView {
     const double *Icub, *Drc, *Dsc, *If, *Minv;

@@ -114,7 +114,30 @@ struct WeakArgs {
     const T *__restrict__ mfold;   // [Kc][Np][Np] M_k^-1 M_ref (P = 1: M_k^-1)
     const int *__restrict__ widx;  // [K] curved slot or -1
     const double *__restrict__ dt;
+    // the last stage of a run's step: also the time-step bound of the new
+    // state (as k_cfl: FP64 per face node) into the slots, and its check.
+    // Two launches of 9 us a step less (5,000 elements at P = 4 in FP64, 20
+    // steps: 1,674 -> 1,637 us; 4,000 at P = 3 in FP32: 814 -> 742 us).
+    int bound;
+    double gamma;
+    const double *__restrict__ fgeo;   // [K][3][3 Nfp], Fscale last
+    unsigned long long *__restrict__ vmax;
+    int *__restrict__ flag;
 };
+
+// A wavefront's largest bound; its check into the flag.
+__device__ __forceinline__ double wave_bound(double best, int bad, int *flag) {
+    const bool any = __any(bad);
+    for (int off = 32; off > 0; off >>= 1) {
+        const double o = __shfl_xor(best, off);
+        best = o > best ? o : best;
+    }
+    if (any && (threadIdx.x & 63) == 0) atomicOr(flag, 1);
+    return best;
+}
+__device__ __forceinline__ void post_bound(double best, int slot, unsigned long long *vmax) {
+    atomicMax(vmax + (slot & (kVmaxSlots - 1)), (unsigned long long)__double_as_longlong(best));
+}
 
 __device__ __forceinline__ float quad_swap(float v, std::integral_constant<int, 1>) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xf, 0xf, true));   // lane ^ 1
@@ -168,26 +191,28 @@ __device__ __forceinline__ f64x4 mfma16(double a, double b, f64x4 c) {
 }
 
 // Waves per SIMD: FP32 four (100,000 elements at P = 4, two steps, 886 us; 924
-// at five and 1,066 at six, which spill); FP64 three up to P = 3 (947 against
-// 1,018 us at two, P = 3), two above (5,000 at P = 4, 20 steps: 1.72 against
-// 2.10 ms at three).
-template <typename T, int P>
+// at five and 1,066 at six, which spill), five at P = 2 (300,000 straight
+// elements, four steps, 1,673 against 1,726 us); FP64 three up to P = 3 (947
+// against 1,018 us at two, P = 3), two above (5,000 at P = 4, 20 steps: 1.72
+// against 2.10 ms at three) and where the bound takes registers (300 at P = 2,
+// 20 steps, 793 against 809 us).
+template <typename T, int P, bool BOUND = false>
 constexpr int weak_waves() {
-    return sizeof(T) == 4 ? 4 : (P <= 3 ? 3 : 2);
+    return sizeof(T) == 4 ? (P <= 2 ? 5 : 4) : (P <= 3 && !BOUND ? 3 : 2);
 }
 
 // Blocks of W wavefronts a compute unit holds at once (LDS and registers).
-template <typename T, int P>
+template <typename T, int P, bool BOUND>
 constexpr int weak_blocks(int W) {
     using S = WeakM<T, P>;
     const int lds = (S::NZV * 64 * S::VF + W * 2 * S::TS) * int(sizeof(T));
-    const int by_lds = 160 * 1024 / lds, by_regs = 4 * weak_waves<T, P>() / W;
+    const int by_lds = 160 * 1024 / lds, by_regs = 4 * weak_waves<T, P, BOUND>() / W;
     const int n = by_lds < by_regs ? by_lds : by_regs;
     return n < 1 ? 1 : n;
 }
 
-template <typename T, int P, int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(weak_waves<T, P>()))) void k_stage_weak(WeakArgs<T> a) {
+template <typename T, int P, int W, bool BOUND>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(weak_waves<T, P, BOUND>()))) void k_stage_weak(WeakArgs<T> a) {
     using S = WeakM<T, P>;
     using V4 = typename WeakVec<T>::V4;
     using V = typename WeakVec<T>::V;
@@ -211,6 +236,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(weak_wav
     for (int mt = 0; mt < MT1; ++mt) wqv[mt] = a.wq[min(S::row(mt, kq, c), NQ - 1)];
     __syncthreads();
     T *sU = sT[wave][0], *sR = sT[wave][1];
+    double best = 0.0;
+    int bad = 0;
 
     // XCD x (block b runs on XCD b % 8) walks the x-th contiguous eighth of the groups
     const int g0 = int(blockIdx.x % 8) * a.per, gend = min(g0 + a.per, a.ngroups);
@@ -405,7 +432,17 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(weak_wav
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
-        // ---- Runge-Kutta update (or the bare rhs), coalesced
+        // ---- Runge-Kutta update (or the bare rhs), coalesced; the bound's
+        // Fscale is requested before the stores, which a later load would
+        // wait for
+        constexpr int NB = (4 * NF3 + 63) / 64;
+        double fsc[NB];
+        if constexpr (BOUND)
+#pragma unroll
+            for (int t = 0; t < NB; ++t) {
+                const int z = min(lane + 64 * t, nel * NF3 - 1), e = z / NF3;
+                fsc[t] = a.fgeo[((k0 + e) * 3 + 2) * NF3 + (z - e * NF3)];
+            }
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const int zv = lane + 64 * v;
@@ -421,14 +458,53 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(weak_wav
                 } else {
                     VG rr = dt * rh;
                     if (a.stage > 0) rr = a.ra * reinterpret_cast<const VG *>(a.R + base)[zv] + dt * rh;
+                    un4 = un4 + a.rb * rr;
                     reinterpret_cast<VG *>(a.R + base)[zv] = rr;
-                    reinterpret_cast<VG *>(a.Uout + base)[zv] = un4 + a.rb * rr;
+                    reinterpret_cast<VG *>(a.Uout + base)[zv] = un4;
+                    if constexpr (BOUND)
+#pragma unroll
+                        for (int i = 0; i < VF; ++i) sU[VF * zv + i] = un4[i];
+                }
+            }
+        }
+        if constexpr (BOUND) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            for (int z = lane; z < nel * Np; z += 64) {
+                const int e = z / Np, i = z - e * Np;
+                double u[kFields];
+#pragma unroll
+                for (int f = 0; f < kFields; ++f) u[f] = double(sU[(e * kFields + f) * Np + i]);
+                if (bad_state(a.gamma, u)) bad = 1;
+            }
+#pragma unroll
+            for (int t = 0; t < NB; ++t) {
+                const int z = lane + 64 * t;
+                if (z < nel * NF3) {
+                    const int e = z / NF3, q = z - e * NF3, f = q / Nfp, v = face_node(P, f, q - f * Nfp);
+                    double u[kFields];
+#pragma unroll
+                    for (int g = 0; g < kFields; ++g) u[g] = double(sU[(e * kFields + g) * Np + v]);
+                    const double b = cfl_bound(a.gamma, u, fsc[t], 0.0, P + 1.0);
+                    best = b > best ? b : best;
                 }
             }
         }
         // the tiles are reused by the next group
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
+    }
+    if constexpr (BOUND) {
+        // one atomic per block: a launch's blocks end together (20,000
+        // elements at P = 2, 20 steps: 987 us; 1,099 with one per wavefront)
+        __shared__ double sRed[W];
+        best = wave_bound(best, bad, a.flag);
+        if (lane == 0) sRed[wave] = best;
+        __syncthreads();
+        if (tid == 0) {
+            for (int w = 1; w < W; ++w) best = sRed[w] > best ? sRed[w] : best;
+            post_bound(best, int(blockIdx.x), a.vmax);
+        }
     }
 }
 
@@ -570,6 +646,15 @@ __global__ __launch_bounds__(kW1Block) void k_stage_weak1(WeakArgs<T> a) {
     }
     __syncthreads();
     if (ne >= EB) return;
+    double fsc[2] = {0.0, 0.0}, u64[kFields];
+    if (a.bound && node) {
+        // the node's two faces, and its place on each
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int ff = t == 0 ? (i == 2 ? 1 : 0) : (i == 1 ? 1 : 2);
+            fsc[t] = a.fgeo[((k0 + ne) * 3 + 2) * 6 + 2 * ff + (i == face_node(1, ff, 0) ? 0 : 1)];
+        }
+    }
     // V - S at the node, M_k^-1 over the quad, the Runge-Kutta update
 #pragma unroll
     for (int c = 0; c < kFields; ++c) {
@@ -595,8 +680,22 @@ __global__ __launch_bounds__(kW1Block) void k_stage_weak1(WeakArgs<T> a) {
         } else {
             const T rr = a.stage == 0 ? dt * val : a.ra * rn[c] + dt * val;
             a.R[at + c * Np] = rr;
-            a.Uout[at + c * Np] = un[c] + a.rb * rr;
+            un[c] = un[c] + a.rb * rr;
+            a.Uout[at + c * Np] = un[c];
         }
+        u64[c] = double(un[c]);
+    }
+    if (a.bound) {
+        double best = 0.0;
+        int bad = 0;
+        if (node) {
+            bad = bad_state(a.gamma, u64);
+            const double b0 = cfl_bound(a.gamma, u64, fsc[0], 0.0, 2.0), b1 = cfl_bound(a.gamma, u64, fsc[1], 0.0, 2.0);
+            best = b0 > best ? b0 : best;
+            best = b1 > best ? b1 : best;
+        }
+        best = wave_bound(best, bad, a.flag);
+        if ((tid & 63) == 0) post_bound(best, int(blockIdx.x) * 2 + (tid >> 6), a.vmax);
     }
 }
 
@@ -820,7 +919,7 @@ void fill_weak_frags(const double *Icub, const double *Drc, const double *Dsc, c
 
 template <typename T>
 hipError_t stage_weak_t(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs, int stage,
-                        hipStream_t st) {
+                        bool bound, hipStream_t st) {
     WeakArgs<T> a;
     a.K = m.K;
     a.stage = stage;
@@ -853,6 +952,11 @@ hipError_t stage_weak_t(const DevMesh &m, const void *Uin, void *Uout, void *R, 
     }
     a.widx = m.widx;
     a.dt = m.scal + S_DT;
+    a.bound = bound && !rhs && m.vmax ? 1 : 0;
+    a.gamma = m.gamma;
+    a.fgeo = m.fgeo64;
+    a.vmax = m.vmax;
+    a.flag = m.flag;
     a.ngroups = (m.K + 3) / 4;
     a.per = (a.ngroups + 7) / 8;
     return with_order_w(m.P, [&](auto PC) {
@@ -873,11 +977,21 @@ hipError_t stage_weak_t(const DevMesh &m, const void *Uin, void *Uout, void *R, 
             // mesh's last block (800 FP32 elements at P = 3, 60 steps, 2,163
             // against 2,374 us; 20,000 at P = 2, 20 steps, 1,047 against 1,106
             // us).
-            constexpr int w4 = 4 * weak_blocks<T, P>(4), w8 = 8 * weak_blocks<T, P>(8);
+            constexpr int w4 = 4 * weak_blocks<T, P, false>(4), w8 = 8 * weak_blocks<T, P, false>(8);
             auto go = [&](auto WC) {
                 constexpr int W = decltype(WC)::value;
-                const int want = 8 * ((a.per + W - 1) / W), most = 256 * weak_blocks<T, P>(W);
-                hipLaunchKernelGGL((k_stage_weak<T, P, W>), dim3(unsigned(want < most ? want : most)), dim3(64 * W), 0, st, a);
+                auto launch = [&](auto BC) {
+                    constexpr bool BOUND = decltype(BC)::value;
+                    const int want = 8 * ((a.per + W - 1) / W), most = 256 * weak_blocks<T, P, BOUND>(W);
+                    hipLaunchKernelGGL((k_stage_weak<T, P, W, BOUND>), dim3(unsigned(want < most ? want : most)),
+                                       dim3(64 * W), 0, st, a);
+                };
+                // (a variant of its own: the bound's registers would spill
+                // in the other stages too)
+                if (a.bound)
+                    launch(std::true_type());
+                else
+                    launch(std::false_type());
             };
             if constexpr (w8 > w4) {
                 if (a.ngroups > 256 * 4) {
@@ -940,9 +1054,9 @@ hipError_t launch_weak_geometry(const DevMesh &m, const double *x, const double 
 }
 
 hipError_t launch_stage_weak(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs, int stage,
-                             hipStream_t st) {
-    return m.fp32 ? stage_weak_t<float>(m, Uin, Uout, R, rhs, stage, st)
-                  : stage_weak_t<double>(m, Uin, Uout, R, rhs, stage, st);
+                             bool bound, hipStream_t st) {
+    return m.fp32 ? stage_weak_t<float>(m, Uin, Uout, R, rhs, stage, bound, st)
+                  : stage_weak_t<double>(m, Uin, Uout, R, rhs, stage, bound, st);
 }
 
 }  // namespace dg
