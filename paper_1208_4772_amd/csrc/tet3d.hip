@@ -154,11 +154,14 @@ struct Stage3MArgs {
     int *__restrict__ flag;
 };
 
-// The stage body for FP32 (k_stage3_mfma) and FP64 (k_stage3_mfma64).  FP32
-// keeps each node's pointwise fluxes in registers across the three direction
-// passes and requests the Runge-Kutta register before the product; FP64
-// (twice the registers per value) recomputes the fluxes per pass and reads
-// the register in the epilogue.
+// The stage body for FP32 (k_stage3_mfma) and FP64 (k_stage3_mfma64).  Each
+// node's pointwise fluxes stay in registers across the three direction passes
+// and the Runge-Kutta register is requested before the product, except in
+// FP64 at P = 4 (two nodes per thread, 60 registers, where 124 already limit
+// the wavefronts): it recomputes the fluxes per pass and reads the register in
+// the epilogue.  FP64 at P = 3, 24,576 tetrahedra, ten steps: 1,829 us with
+// the fluxes recomputed and the register read late, 1,791 with the fluxes
+// kept, 1,757 with both (LDS holds four blocks on a CU either way).
 template <typename T, int P>
 __device__ __forceinline__ void stage3_mfma_body(const Stage3MArgs<T> &a) {
     using S = TetM<P>;
@@ -166,6 +169,7 @@ __device__ __forceinline__ void stage3_mfma_body(const Stage3MArgs<T> &a) {
     using V16 = typename VT<T>::V16;
     constexpr int VW = VT<T>::VW;
     constexpr bool F32 = sizeof(T) == 4;
+    constexpr bool KEEP = F32 || P <= 3;   // fluxes and the Runge-Kutta register ahead of their use
     constexpr int Np = S::Np, NF4 = S::NF4, KSD = S::KSD, KSL = S::KSL, KPP = S::KPP, MT = S::MT;
     constexpr int W = S::W, NTH = S::NTH, NT = S::NT, GW = S::GW, EB = S::EB, NGD = S::NGD, NGL = S::NGL;
     constexpr int TPT = S::TPT, PPT = S::PPT;
@@ -267,11 +271,10 @@ __device__ __forceinline__ void stage3_mfma_body(const Stage3MArgs<T> &a) {
     }
 #pragma unroll
     for (int g = 0; g < NG; ++g) ga[g] = a.opsA[g * 64 + lane];
-    // FP32: the pointwise fluxes of this thread's nodes, kept in registers
-    // for the three direction passes
-    constexpr int KP_ = F32 ? PPT : 1;
+    // the pointwise fluxes of this thread's nodes, for the three direction passes
+    constexpr int KP_ = KEEP ? PPT : 1;
     T Fx[KP_][kF3], Fy[KP_][kF3], Fz[KP_][kF3];
-    if constexpr (F32) {
+    if constexpr (KEEP) {
 #pragma unroll
         for (int p = 0; p < PPT; ++p) {
             const int z = min(tid + p * NTH, nel * Np - 1);
@@ -305,7 +308,7 @@ __device__ __forceinline__ void stage3_mfma_body(const Stage3MArgs<T> &a) {
                 const T m0 = m[0], m1 = m[1], m2 = m[2];
                 T(*B)[KPP] = sB[el / 3];
                 const int col = (el % 3) * kF3;
-                if constexpr (F32) {
+                if constexpr (KEEP) {
 #pragma unroll
                     for (int c = 0; c < kF3; ++c) B[col + c][i] = m0 * Fx[p][c] + m1 * Fy[p][c] + m2 * Fz[p][c];
                 } else {
@@ -323,10 +326,10 @@ __device__ __forceinline__ void stage3_mfma_body(const Stage3MArgs<T> &a) {
         __syncthreads();
         product(ga, std::integral_constant<int, KSD>());
     }
-    constexpr int NR = F32 ? NV : 1;
+    constexpr int NR = KEEP ? NV : 1;
     V16 rv[NR];
     const bool rk_read = a.mode && a.stage > 0;
-    if constexpr (F32) {
+    if constexpr (KEEP) {
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const int z = min(tid + v * NTH, nv - 1);
@@ -371,7 +374,7 @@ __device__ __forceinline__ void stage3_mfma_body(const Stage3MArgs<T> &a) {
                 reinterpret_cast<V16 *>(a.rhs + base)[zv] = rh;
             } else {
                 V16 rold;
-                if constexpr (F32)
+                if constexpr (KEEP)
                     rold = rv[v];
                 else
                     rold = rk_read ? reinterpret_cast<const V16 *>(a.R + base)[zv] : V16{};
