@@ -61,9 +61,10 @@ enum dg_status {
 };
 
 /* There is no separate DG_FP64 = 1: FP64 handles use DG_FP64_PLAIN, FP64
- * throughout.  Its stage runs on the VALUs, except for meshes whose elements
- * are all straight and carry no artificial viscosity, where the stage's
- * product runs on the FP64 matrix cores (v_mfma_f64_16x16x4f64). */
+ * throughout.  Its stage's product runs on the FP64 matrix cores
+ * (v_mfma_f64_16x16x4f64), except on meshes with curved elements or
+ * artificial viscosity below P = 3 and on small ones of these at P = 4 and 5,
+ * where it runs on the VALUs. */
 enum dg_precision {
     DG_FP64_PLAIN = 0,   /* FP64 throughout */
     DG_FP32 = 2,         /* FP32 state and fused stage kernel; FP64 setup,
@@ -90,8 +91,9 @@ enum dg_riemann { DG_RIEMANN_LF = 0, DG_RIEMANN_HLLC = 1 };
  * collapsed Gauss product rule of n x n points exact for degree 3P
  * (n = (3P+2)/2) and to n Gauss points per face, M_k dU/dt = V - S with the
  * per-element mass matrix (inverted by Cholesky for curved elements at
- * setup).  Inviscid only (av_enable must be 0); FP64 or FP32 state, VALU
- * contractions; time step as for the nodal form. */
+ * setup).  Inviscid only (av_enable must be 0); FP64 or FP32 state, the
+ * contractions on the matrix cores (P = 1: VALUs); time step as for the nodal
+ * form. */
 enum dg_form { DG_FORM_NODAL = 0, DG_FORM_WEAK = 1 };
 
 /* Message of the last error on this thread ("" if none). */
