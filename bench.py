@@ -122,8 +122,8 @@ def stage_kernel_label(case, precision, waves, form="nodal"):
     """The launch(es) one Runge-Kutta stage consists of: the stage kernel, and
     with artificial viscosity the sensor and gradient launches before it
     (their time is in the per-stage average, so their bytes are in the
-    algorithmic figure; a step's first stage runs the sensor that also
-    reduces the time-step bound, k_sensor, in place of k_sensor_elem)."""
+    algorithmic figure; a step's first stage runs the gradient that also
+    reduces the time-step bound)."""
     av = "true" if case.av else "false"
     if form == "weak":
         return f"k_stage_weak<{'double' if precision == 'fp64' else 'float'},{case.P}>"

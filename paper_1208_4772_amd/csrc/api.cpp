@@ -748,7 +748,7 @@ static int step_impl(dg_mesh *m, void *U, void *work, double dt, hipStream_t st,
         // matrix-core path: the first stage turns the CFL bound in
         // vmax[parity] into dt and clears vmax[1 - parity]; without
         // viscosity the previous step's last stage left the bound (of this
-        // step's state), with viscosity this step's first sensor does (it
+        // step's state), with viscosity this step's first gradient does (it
         // needs the viscosity of this state)
         unsigned long long *vin = m->dm.vmax + fused_parity * kVmaxSlots;
         unsigned long long *vout = m->dm.vmax + (1 - fused_parity) * kVmaxSlots;
@@ -765,11 +765,11 @@ static int step_impl(dg_mesh *m, void *U, void *work, double dt, hipStream_t st,
                 ms.vmax_out = vout;
             }
             if (m->dm.av) {
+                HIP_TRY(launch_sensor(m->dm, in[s], eps, st));
                 if (s == 0)
-                    HIP_TRY(launch_sensor_cfl(m->dm, in[0], eps, vin, st));
+                    HIP_TRY(launch_avgrad_cfl(m->dm, in[0], eps, Q, vin, st));
                 else
-                    HIP_TRY(launch_sensor(m->dm, in[s], eps, st));
-                HIP_TRY(launch_avgrad(m->dm, in[s], eps, Q, st));
+                    HIP_TRY(launch_avgrad(m->dm, in[s], eps, Q, st));
             }
             HIP_TRY(m->time_begin(st));
             HIP_TRY(launch_stage_mfma(m->dm, in[s], out[s], R, nullptr, s, ms, st, Q));
@@ -951,7 +951,7 @@ int dg_run(dg_mesh *m, void *U, void *work, int nsteps, dg_run_stats *stats, voi
         }
     }
     HIP_TRY(hipEventRecord(e1, st));
-    // a fused viscous run checks each step's state in its first sensor: the
+    // a fused viscous run checks each step's state in its first gradient: the
     // final state still needs the check
     if (fused && m->dm.av && nsteps > 0) HIP_TRY(launch_cfl_vmax(m->dm, U, m->dm.vmax, st));
     // diagnostics at the end: totals and the residual ||rhs(U)||_inf
@@ -1310,12 +1310,10 @@ struct Group {
     size_t items_cap = 0;          // entries (int2)
     void *eitems = nullptr;        // viscous: (job, block of 256 elements) for the per-element sensor
     size_t eitems_cap = 0;
-    void *aitems = nullptr;        // viscous: (job, tile) of the per-node sensor
-    size_t aitems_cap = 0;
     void *gitems = nullptr;        // viscous: (job, tile) of the gradient
     size_t gitems_cap = 0;
-    int *counts = nullptr;         // device [4]: items, eitems, aitems, gitems
-    int nitems = 0, neitems = 0, naitems = 0, ngitems = 0;
+    int *counts = nullptr;         // device [3]: items, eitems, gitems
+    int nitems = 0, neitems = 0, ngitems = 0;
 };
 
 // Branches of the captured graph.  Groups share no data (state, work, slots
@@ -1361,7 +1359,6 @@ struct dg_batch {
             if (g.avjobs) (void)hipFree(g.avjobs);
             if (g.items) (void)hipFree(g.items);
             if (g.eitems) (void)hipFree(g.eitems);
-            if (g.aitems) (void)hipFree(g.aitems);
             if (g.gitems) (void)hipFree(g.gitems);
             if (g.counts) (void)hipFree(g.counts);
         }
@@ -1404,7 +1401,7 @@ int rebuild(dg_batch *b, hipStream_t st) {
             ng.waves = tw ? tw : mfma_default_waves();
             if (hipMalloc(&ng.jobs, 2 * 5 * max_jobs * mfma_args_bytes()) != hipSuccess ||
                 (av && hipMalloc(&ng.avjobs, 2 * 5 * max_jobs * av_args_bytes()) != hipSuccess) ||
-                hipMalloc(reinterpret_cast<void **>(&ng.counts), 4 * sizeof(int)) != hipSuccess) {
+                hipMalloc(reinterpret_cast<void **>(&ng.counts), 3 * sizeof(int)) != hipSuccess) {
                 if (ng.jobs) (void)hipFree(ng.jobs);
                 if (ng.avjobs) (void)hipFree(ng.avjobs);
                 return fail(DG_ENOMEM, "batch table allocation failed");
@@ -1423,7 +1420,7 @@ int rebuild(dg_batch *b, hipStream_t st) {
         const size_t nj = g.slots.size();
         const size_t rec = mfma_args_bytes(), arec = av_args_bytes();
         std::vector<char> jobs(2 * 5 * max_jobs * rec, 0), avjobs(g.av ? 2 * 5 * max_jobs * arec : 0, 0);
-        std::vector<int> items, eitems, aitems, gitems;
+        std::vector<int> items, eitems, gitems;
         for (size_t j = 0; j < nj; ++j) {
             Slot &s = b->slots[g.slots[j]];
             dg_mesh *m = s.mesh;
@@ -1467,11 +1464,6 @@ int rebuild(dg_batch *b, hipStream_t st) {
                     eitems.push_back(int(j));
                     eitems.push_back(tt);
                 }
-                const int na = av_tiles(m->dm);
-                for (int tt = 0; tt < na; ++tt) {
-                    aitems.push_back(int(j));
-                    aitems.push_back(tt);
-                }
                 const int ng = grad_tiles(m->dm);
                 for (int tt = 0; tt < ng; ++tt) {
                     gitems.push_back(int(j));
@@ -1481,7 +1473,6 @@ int rebuild(dg_batch *b, hipStream_t st) {
         }
         g.nitems = int(items.size() / 2);
         g.neitems = int(eitems.size() / 2);
-        g.naitems = int(aitems.size() / 2);
         g.ngitems = int(gitems.size() / 2);
         // work lists grow by doubling; a new table means a new address, so
         // the captured graph is stale
@@ -1500,7 +1491,6 @@ int rebuild(dg_batch *b, hipStream_t st) {
         if (int rc = grow(&g.items, &g.items_cap, size_t(g.nitems))) return rc;
         if (g.av) {
             if (int rc = grow(&g.eitems, &g.eitems_cap, size_t(g.neitems))) return rc;
-            if (int rc = grow(&g.aitems, &g.aitems_cap, size_t(g.naitems))) return rc;
             if (int rc = grow(&g.gitems, &g.gitems_cap, size_t(g.ngitems))) return rc;
         }
         HIP_TRY(hipMemcpyAsync(g.jobs, jobs.data(), jobs.size(), hipMemcpyHostToDevice, st));
@@ -1509,11 +1499,9 @@ int rebuild(dg_batch *b, hipStream_t st) {
             HIP_TRY(hipMemcpyAsync(g.items, items.data(), items.size() * sizeof(int), hipMemcpyHostToDevice, st));
         if (!eitems.empty())
             HIP_TRY(hipMemcpyAsync(g.eitems, eitems.data(), eitems.size() * sizeof(int), hipMemcpyHostToDevice, st));
-        if (!aitems.empty())
-            HIP_TRY(hipMemcpyAsync(g.aitems, aitems.data(), aitems.size() * sizeof(int), hipMemcpyHostToDevice, st));
         if (!gitems.empty())
             HIP_TRY(hipMemcpyAsync(g.gitems, gitems.data(), gitems.size() * sizeof(int), hipMemcpyHostToDevice, st));
-        const int counts[4] = {g.nitems, g.neitems, g.naitems, g.ngitems};
+        const int counts[3] = {g.nitems, g.neitems, g.ngitems};
         HIP_TRY(hipMemcpyAsync(g.counts, counts, sizeof(counts), hipMemcpyHostToDevice, st));
         // the host buffers go out of scope: wait for the copies
         HIP_TRY(hipStreamSynchronize(st));
@@ -1545,8 +1533,8 @@ int group_step(dg_batch *b, const Group &g, int ps, hipStream_t st) {
     for (int s5 = 0; s5 < 5; ++s5) {
         if (g.av) {
             const char *avjobs = static_cast<const char *>(g.avjobs) + (ps * 5 + s5) * nj * arec;
-            HIP_TRY(launch_av_batch(g.P, s5 == 0, avjobs, g.aitems, g.counts + 2, int(g.aitems_cap), g.eitems,
-                                    g.counts + 1, int(g.eitems_cap), g.gitems, g.counts + 3, int(g.gitems_cap), st));
+            HIP_TRY(launch_av_batch(g.P, s5 == 0, avjobs, g.eitems, g.counts + 1, int(g.eitems_cap), g.gitems,
+                                    g.counts + 2, int(g.gitems_cap), st));
         }
         const char *jobs = static_cast<const char *>(g.jobs) + (ps * 5 + s5) * nj * rec;
         HIP_TRY(launch_stage_mfma_batch(g.P, g.bf3, g.av, g.waves, jobs, g.items, g.counts, int(g.items_cap), st));
@@ -1717,7 +1705,7 @@ int dg_batch_advance(dg_batch *b, int max_steps, void *stream, int *steps_run) {
                 s.finished = true;
                 b->dirty = true;
                 // a batched viscous slot checks each step's state in that
-                // step's first sensor: check the final state as dg_run does
+                // step's first gradient: check the final state as dg_run does
                 if (batched_path(s.mesh) && s.mesh->dm.av)
                     HIP_TRY(launch_cfl_vmax(s.mesh->dm, s.U, s.mesh->dm.vmax, st));
             }

@@ -291,107 +291,17 @@ struct AvArgs {
     const T *__restrict__ emax;
     const T *__restrict__ rec;     // [K][16] geometry records (null: per-node geometry for every element)
     const T *__restrict__ opsG;    // matrix-core fragments of Dr, Ds and LIFT
-    unsigned long long *__restrict__ vmax;   // CFL-bound slots (sensor with the bound only)
-    int *__restrict__ flag;                  // state check (sensor with the bound only)
+    unsigned long long *__restrict__ vmax;   // CFL-bound slots (gradient with the bound only)
+    int *__restrict__ flag;                  // state check (gradient with the bound only)
 };
 
 // Persson-Peraire sensor on the density: u_hat = V^{-1} rho, S = (energy of
 // the degree-P modes) / (total modal energy), s = log10 S, sine ramp of
-// half-width kappa around s0, capped at eps_max,k.  CFL: also the time-step
-// bound of the state with its new viscosity (FP64 per face node, cfl_bound),
-// reduced into the block's slot, and the state check (rho, p > 0, finite).
-template <typename T, int P, bool CFL>
-__device__ __forceinline__ void sensor_body(const AvArgs<T> &a, const int tile) {
-    using O = Order<P>;
-    constexpr int Np = O::Np, Nfp = O::Nfp, NF3 = O::Nface, EB = O::EB;
-    __shared__ T sR[EB][Np];
-    __shared__ double sE[EB][Np];
-    __shared__ T sEps[EB];
-    __shared__ double sRed[kBlock / 64];
-    // V^{-1} staged once per block: every thread reads a row of it, and
-    // reading it through the caches costs a memory instruction per entry
-    __shared__ T sVi[Np * Np];
-    LdsCopy<T, Np * Np> vic;
-    vic.load(a.ops + (2 * Np * Np + Np * 3 * Nfp));
-    Tile<P> t(a.K, tile);
-    if (t.act) sR[t.el][t.i] = a.U[(t.k * kFields + 0) * Np + t.i];
-    vic.store(sVi);
-    __syncthreads();
-    if (t.act) {
-        T uh = 0;
-#pragma unroll
-        for (int j = 0; j < Np; ++j) uh += sVi[t.i * Np + j] * sR[t.el][j];
-        sE[t.el][t.i] = double(uh) * double(uh);
-    }
-    __syncthreads();
-    if (t.act && t.i == 0) {
-        double num = 0, den = 0;
-#pragma unroll
-        for (int j = 0; j < Np; ++j) {
-            den += sE[t.el][j];
-            if (j >= Np - Nfp) num += sE[t.el][j];
-        }
-        double emax = double(a.emax[t.k]);
-        double e = 0.0;
-        if (den > 1e-300 && num > 0.0) {
-            double sk = log10(num / den);
-            if (sk > a.s0 + a.kappa)
-                e = emax;
-            else if (sk >= a.s0 - a.kappa)
-                e = 0.5 * emax * (1.0 + sin(M_PI * (sk - a.s0) / (2.0 * a.kappa)));
-        }
-        a.eps_out[t.k] = T(e);
-        if constexpr (CFL) sEps[t.el] = T(e);
-    }
-    if constexpr (CFL) {
-        __syncthreads();
-        double vmax = 0.0;
-        int bad = 0;
-        if (t.act) {
-            const T *Uk = a.U + t.k * kFields * Np;
-            {
-                double u[kFields];
-#pragma unroll
-                for (int c = 0; c < kFields; ++c) u[c] = double(Uk[c * Np + t.i]);
-                if (bad_state(a.gamma, u)) bad = 1;
-            }
-            const double P1 = P + 1.0, e = double(sEps[t.el]);
-            for (int q = t.i; q < NF3; q += Np) {
-                const int v = face_node(P, q / Nfp, q % Nfp);
-                double u[kFields];
-#pragma unroll
-                for (int c = 0; c < kFields; ++c) u[c] = double(Uk[c * Np + v]);
-                const double val = cfl_bound(a.gamma, u, double(a.fgeo[(t.k * 3 + 2) * NF3 + q]), e, P1);
-                vmax = val > vmax ? val : vmax;
-            }
-        }
-        if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(a.flag, 1);
-        for (int off = 32; off > 0; off >>= 1) {
-            const double o = __shfl_xor(vmax, off);
-            vmax = o > vmax ? o : vmax;
-        }
-        if ((threadIdx.x & 63) == 0) sRed[threadIdx.x >> 6] = vmax;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double m = sRed[0];
-            for (int w = 1; w < kBlock / 64; ++w) m = sRed[w] > m ? sRed[w] : m;
-            // non-negative doubles order like their bit patterns
-            atomicMax(a.vmax + (blockIdx.x & (kVmaxSlots - 1)), (unsigned long long)__double_as_longlong(m));
-        }
-    }
-}
-
-template <typename T, int P, bool CFL>
-__global__ __launch_bounds__(kBlock) void k_sensor(AvArgs<T> a) {
-    sensor_body<T, P, CFL>(a, blockIdx.x);
-}
-
-// The sensor alone (no time-step bound) with one thread per element: the
-// block copies the densities of its kBlock elements into LDS (contiguous
+// half-width kappa around s0, capped at eps_max,k.  One thread per element:
+// the block copies the densities of its kBlock elements into LDS (contiguous
 // runs of Np values, all loads issued before the first wait), then each
-// thread forms its element's modal energies and viscosity with the same
-// operations in the same order as sensor_body, so the results are the same
-// bits, without the two block-wide phases per element.
+// thread forms its element's modal energies and viscosity, without block-wide
+// phases per element.
 template <typename T, int P>
 __device__ __forceinline__ void sensor_elem_body(const AvArgs<T> &a, const int tile) {
     using O = Order<P>;
@@ -502,7 +412,14 @@ __device__ __forceinline__ f64x4 mfma16(double a, double b, f64x4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-template <typename T, int P>
+// CFL (a step's first stage): also the time-step bound of the state with its
+// viscosity (FP64 per face node, cfl_bound) into the block's slot and the
+// state check, from the tile in LDS while the operators are on their way.  A
+// sensor that reduced the bound (a thread per node, four block-wide phases)
+// took 23 us against the 6 of the sensor alone (120,000 elements, P = 3, ten
+// steps: 3,254 us with it, 3,177 with the bound here; 2,000 at P = 5, where
+// the chain of a block is what counts, 20 steps: 1,954 and 2,003).
+template <typename T, int P, bool CFL>
 __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) {
     using S = GradShape<T, P>;
     using V4 = typename Vec<T>::V4;
@@ -512,7 +429,8 @@ __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) 
     __shared__ __attribute__((aligned(16))) T sU[EB * kFields * Np];
     __shared__ __attribute__((aligned(16))) T sW[S::NT * RG];
     __shared__ __attribute__((aligned(16))) T sG[EB][16];
-    __shared__ T sSig[EB];
+    __shared__ T sSig[EB], sEps[CFL ? EB : 1];
+    __shared__ double sRed[kBlock / 64];
     const long k0 = (long)tile * EB;
     const unsigned nel = (unsigned)min((long)EB, (long)a.K - k0);
     const unsigned tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -533,6 +451,13 @@ __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) 
         info[t] = ft[e];
         nb[t] = nt[e * 3 + f];
     }
+    T fsc[TPT];
+    if constexpr (CFL)
+#pragma unroll
+        for (int t = 0; t < TPT; ++t) {
+            const unsigned task = min(tid + t * kBlock, ntask - 1), e = task / NF3;
+            fsc[t] = a.fgeo[((k0 + e) * 3 + 2) * NF3 + (task - e * NF3)];
+        }
     V16 uv[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) uv[v] = reinterpret_cast<const V16 *>(Ut)[min(tid + v * kBlock, nv - 1)];
@@ -572,7 +497,10 @@ __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) 
             for (int e = 0; e < VW; ++e) (&sG[0][0])[VW * z + e] = gv[v][e];
         }
     }
-    if (tid < nel) sSig[tid] = sqrt(ev);
+    if (tid < nel) {
+        sSig[tid] = sqrt(ev);
+        if constexpr (CFL) sEps[tid] = ev;
+    }
     __syncthreads();
 
     // jumps Fscale n ((sigma U)* - sigma U-) at the face nodes, column-major
@@ -612,7 +540,44 @@ __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) 
     V4 ga[NG];
 #pragma unroll
     for (int g = 0; g < NG; ++g) ga[g] = reinterpret_cast<const V4 *>(a.opsG)[g * 64 + lane];
+    if constexpr (CFL) {
+        double best = 0.0;
+        int bad = 0;
+        for (unsigned z = tid; z < nel * Np; z += kBlock) {
+            const unsigned e = z / Np, i = z - e * Np;
+            double u[kFields];
+#pragma unroll
+            for (int c = 0; c < kFields; ++c) u[c] = double(sU[(e * kFields + c) * Np + i]);
+            if (bad_state(a.gamma, u)) bad = 1;
+        }
+#pragma unroll
+        for (int t = 0; t < TPT; ++t) {
+            const unsigned task = tid + t * kBlock;
+            if (task < ntask) {
+                const unsigned e = task / NF3, q = task - e * NF3, f = q / Nfp;
+                const int vm = face_node(P, f, q - f * Nfp);
+                double u[kFields];
+#pragma unroll
+                for (int c = 0; c < kFields; ++c) u[c] = double(sU[(e * kFields + c) * Np + vm]);
+                const double val = cfl_bound(a.gamma, u, double(fsc[t]), double(sEps[e]), P + 1.0);
+                best = val > best ? val : best;
+            }
+        }
+        if (__any(bad) && lane == 0) atomicOr(a.flag, 1);
+        for (int off = 32; off > 0; off >>= 1) {
+            const double o = __shfl_xor(best, off);
+            best = o > best ? o : best;
+        }
+        if (lane == 0) sRed[wave] = best;
+    }
     __syncthreads();
+    if constexpr (CFL)
+        if (tid == 0) {
+            double m = sRed[0];
+            for (int w = 1; w < kBlock / 64; ++w) m = sRed[w] > m ? sRed[w] : m;
+            // non-negative doubles order like their bit patterns
+            atomicMax(a.vmax + (blockIdx.x & (kVmaxSlots - 1)), (unsigned long long)__double_as_longlong(m));
+        }
 
     const unsigned col = lane & 15, kq = lane >> 4;
 #pragma unroll
@@ -705,28 +670,18 @@ constexpr int grad_waves() {
     return w < cap ? (w < 1 ? 1 : w) : cap;
 }
 
-template <typename T, int P>
+template <typename T, int P, bool CFL>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(grad_waves<T, P>()))) void k_avgrad(AvArgs<T> a) {
     const int tile = xcd_tile(a.gchunk);
-    if (tile < a.ngrad) avgrad_body<T, P>(a, tile);
+    if (tile < a.ngrad) avgrad_body<T, P, CFL>(a, tile);
 }
 
 // Batched meshes of one order (FP32 viscous handles): work item = (job,
-// tile), a job being one mesh's argument record for this stage.
+// tile), a job being one mesh's argument record for this stage (sensor: a tile
+// is a block of kBlock elements).
 // One work item per block; the grid covers the list's capacity and the
 // length is read from device memory (a captured launch stays valid when the
 // list changes); surplus blocks exit.
-template <int P, bool CFL>
-__global__ __launch_bounds__(kBlock) void k_sensor_batch(const AvArgs<float> *__restrict__ jobs,
-                                                         const int2 *__restrict__ items,
-                                                         const int *__restrict__ nitems_dev) {
-    const int w = int(blockIdx.x);
-    if (w >= *nitems_dev) return;
-    const int2 it = items[w];
-    sensor_body<float, P, CFL>(jobs[it.x], it.y);
-}
-
-// Batched per-element sensor: work item = (job, block of kBlock elements).
 template <int P>
 __global__ __launch_bounds__(kBlock) void k_sensor_elem_batch(const AvArgs<float> *__restrict__ jobs,
                                                               const int2 *__restrict__ items,
@@ -737,7 +692,7 @@ __global__ __launch_bounds__(kBlock) void k_sensor_elem_batch(const AvArgs<float
     sensor_elem_body<float, P>(jobs[it.x], it.y);
 }
 
-template <int P>
+template <int P, bool CFL>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(grad_waves<float, P>()))) void k_avgrad_batch(const AvArgs<float> *__restrict__ jobs,
                                                          const int2 *__restrict__ items,
                                                          const int *__restrict__ nitems_dev) {
@@ -745,7 +700,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(grad_wav
     const int w = int(blockIdx.x % 8) * per + i;
     if (i >= per || w >= n) return;
     const int2 it = items[w];
-    avgrad_body<float, P>(jobs[it.x], it.y);
+    avgrad_body<float, P, CFL>(jobs[it.x], it.y);
 }
 
 // ---------------------------------------------------------------------------
@@ -1265,31 +1220,19 @@ hipError_t launch_stage(const DevMesh &m, const void *Uin, void *Uout, void *R, 
 }
 
 template <typename T>
-static hipError_t sensor_t(const DevMesh &m, const void *U, void *eps, unsigned long long *vmax,
-                           hipStream_t st) {
+static hipError_t sensor_t(const DevMesh &m, const void *U, void *eps, hipStream_t st) {
     AvArgs<T> a = av_args<T>(m);
     a.U = static_cast<const T *>(U);
     a.eps_out = static_cast<T *>(eps);
-    a.vmax = vmax;
     return with_order(m.P, [&](auto PC) {
         constexpr int P = decltype(PC)::value;
-        if (vmax)
-            hipLaunchKernelGGL((k_sensor<T, P, true>), dim3(nblocks<P>(m.K)), dim3(kBlock), 0, st, a);
-        else
-            hipLaunchKernelGGL((k_sensor_elem<T, P>), dim3((m.K + kBlock - 1) / kBlock), dim3(kBlock), 0, st,
-                               a);
+        hipLaunchKernelGGL((k_sensor_elem<T, P>), dim3((m.K + kBlock - 1) / kBlock), dim3(kBlock), 0, st, a);
         return hipGetLastError();
     });
 }
 
 hipError_t launch_sensor(const DevMesh &m, const void *U, void *eps, hipStream_t st) {
-    return m.fp32 ? sensor_t<float>(m, U, eps, nullptr, st) : sensor_t<double>(m, U, eps, nullptr, st);
-}
-
-hipError_t launch_sensor_cfl(const DevMesh &m, const void *U, void *eps, unsigned long long *vmax,
-                             hipStream_t st) {
-    if (!m.fp32) return hipErrorInvalidValue;
-    return sensor_t<float>(m, U, eps, vmax, st);
+    return m.fp32 ? sensor_t<float>(m, U, eps, st) : sensor_t<double>(m, U, eps, st);
 }
 
 size_t av_args_bytes() { return sizeof(AvArgs<float>); }
@@ -1305,8 +1248,6 @@ void av_fill_args(const DevMesh &m, const void *U, void *eps, void *Q, unsigned 
 }
 
 int sensor_elem_blocks(const DevMesh &m) { return (m.K + kBlock - 1) / kBlock; }
-
-int av_tiles(const DevMesh &m) { return nblocks_rt(m.K, m.P); }
 
 int grad_tiles(const DevMesh &m) {
     int eb = 16;   // elements per block
@@ -1357,43 +1298,51 @@ void grad_fill_opsG64(int P, const double *Dr, const double *Ds, const double *L
     fill_opsG<double>(P, Dr, Ds, LIFT, out);
 }
 
-hipError_t launch_av_batch(int P, bool cfl, const void *jobs, const void *items, const int *nitems_dev,
-                           int capacity, const void *eitems, const int *neitems_dev, int ecapacity,
-                           const void *gitems, const int *ngitems_dev, int gcapacity, hipStream_t st) {
-    if (capacity <= 0) return hipSuccess;
+hipError_t launch_av_batch(int P, bool cfl, const void *jobs, const void *eitems, const int *neitems_dev,
+                           int ecapacity, const void *gitems, const int *ngitems_dev, int gcapacity,
+                           hipStream_t st) {
+    if (ecapacity <= 0 || gcapacity <= 0) return hipSuccess;
     const auto *git = static_cast<const int2 *>(gitems);
     const auto *j = static_cast<const AvArgs<float> *>(jobs);
-    const auto *it = static_cast<const int2 *>(items);
     const auto *eit = static_cast<const int2 *>(eitems);
     return with_order(P, [&](auto PC) {
         constexpr int PP = decltype(PC)::value;
-        if (cfl)
-            hipLaunchKernelGGL((k_sensor_batch<PP, true>), dim3(capacity), dim3(kBlock), 0, st, j, it, nitems_dev);
-        else if (ecapacity > 0)
-            hipLaunchKernelGGL((k_sensor_elem_batch<PP>), dim3(ecapacity), dim3(kBlock), 0, st, j, eit,
-                               neitems_dev);
+        hipLaunchKernelGGL((k_sensor_elem_batch<PP>), dim3(ecapacity), dim3(kBlock), 0, st, j, eit, neitems_dev);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_avgrad_batch<PP>), dim3(unsigned((gcapacity + 7) / 8 * 8)), dim3(kBlock), 0, st, j, git, ngitems_dev);
+        const dim3 grid(unsigned((gcapacity + 7) / 8 * 8));
+        if (cfl)
+            hipLaunchKernelGGL((k_avgrad_batch<PP, true>), grid, dim3(kBlock), 0, st, j, git, ngitems_dev);
+        else
+            hipLaunchKernelGGL((k_avgrad_batch<PP, false>), grid, dim3(kBlock), 0, st, j, git, ngitems_dev);
         return hipGetLastError();
     });
 }
 
-template <typename T>
-static hipError_t avgrad_t(const DevMesh &m, const void *U, const void *eps, void *Q, hipStream_t st) {
+template <typename T, bool CFL>
+static hipError_t avgrad_t(const DevMesh &m, const void *U, const void *eps, void *Q, unsigned long long *vmax,
+                           hipStream_t st) {
     AvArgs<T> a = av_args<T>(m);
     a.U = static_cast<const T *>(U);
     a.eps_in = static_cast<const T *>(eps);
     a.Q = static_cast<T *>(Q);
+    a.vmax = vmax;
     return with_order(m.P, [&](auto PC) {
         constexpr int P = decltype(PC)::value;
-        hipLaunchKernelGGL((k_avgrad<T, P>), dim3(xcd_grid(grad_tiles(m))), dim3(kBlock), 0, st, a);
+        hipLaunchKernelGGL((k_avgrad<T, P, CFL>), dim3(xcd_grid(grad_tiles(m))), dim3(kBlock), 0, st, a);
         return hipGetLastError();
     });
 }
 
 hipError_t launch_avgrad(const DevMesh &m, const void *U, const void *eps, void *Q, hipStream_t st) {
-    return m.fp32 ? avgrad_t<float>(m, U, eps, Q, st) : avgrad_t<double>(m, U, eps, Q, st);
+    return m.fp32 ? avgrad_t<float, false>(m, U, eps, Q, nullptr, st)
+                  : avgrad_t<double, false>(m, U, eps, Q, nullptr, st);
+}
+
+hipError_t launch_avgrad_cfl(const DevMesh &m, const void *U, const void *eps, void *Q, unsigned long long *vmax,
+                             hipStream_t st) {
+    if (!m.fp32) return hipErrorInvalidValue;
+    return avgrad_t<float, true>(m, U, eps, Q, vmax, st);
 }
 
 template <typename T>

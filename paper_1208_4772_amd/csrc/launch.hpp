@@ -179,27 +179,25 @@ hipError_t launch_pack_geometry(const DevMesh &m, const int *cidx, float *geoA, 
 
 // sensor: eps [K] (state precision) from U
 hipError_t launch_sensor(const DevMesh &m, const void *U, void *eps, hipStream_t st);
-// FP32 handles: the sensor plus the CFL bound of U with its new viscosity
-// (FP32 per face node) reduced into the slots vmax[kVmaxSlots] (which must
-// hold zeros or smaller bounds), and the state check into *flag
-hipError_t launch_sensor_cfl(const DevMesh &m, const void *U, void *eps, unsigned long long *vmax,
-                             hipStream_t st);
 // LDG auxiliary gradient from U and eps, as sigma Q [K][Np][8]
 hipError_t launch_avgrad(const DevMesh &m, const void *U, const void *eps, void *Q, hipStream_t st);
+// FP32: also the time-step bound of U and eps (FP64 per face node) into the
+// slots vmax[kVmaxSlots] (which hold zeros or smaller bounds), and the state
+// check into *flag
+hipError_t launch_avgrad_cfl(const DevMesh &m, const void *U, const void *eps, void *Q, unsigned long long *vmax,
+                             hipStream_t st);
 // batched FP32 viscous handles of order P: per-(mesh, stage) argument
 // records and the (record, tile) work list of the stage kernel's batch;
-// one launch of the sensor (with the CFL bound when cfl) and one of the
-// gradient over all of them
+// one launch of the sensor and one of the gradient (with the CFL bound when
+// cfl) over all of them
 size_t av_args_bytes();
 void av_fill_args(const DevMesh &m, const void *U, void *eps, void *Q, unsigned long long *vmax, void *out);
-// items: (job, tile) pairs of the per-node sensor's tiles (av_tiles per
-// mesh); eitems: (job, block) pairs of blocks of 256 elements for the
-// per-element sensor; gitems: the gradient's tiles (grad_tiles per mesh)
-hipError_t launch_av_batch(int P, bool cfl, const void *jobs, const void *items, const int *nitems_dev,
-                           int capacity, const void *eitems, const int *neitems_dev, int ecapacity,
-                           const void *gitems, const int *ngitems_dev, int gcapacity, hipStream_t st);
+// eitems: (job, block) pairs of blocks of 256 elements for the sensor; gitems:
+// (job, tile) pairs of the gradient's tiles (grad_tiles per mesh)
+hipError_t launch_av_batch(int P, bool cfl, const void *jobs, const void *eitems, const int *neitems_dev,
+                           int ecapacity, const void *gitems, const int *ngitems_dev, int gcapacity,
+                           hipStream_t st);
 int sensor_elem_blocks(const DevMesh &m);
-int av_tiles(const DevMesh &m);
 int grad_tiles(const DevMesh &m);
 // matrix-core fragments of the gradient's operators
 size_t grad_opsG_values(int P);

@@ -28,7 +28,7 @@
 // the CFL bound of the new state (FP64 per node from the FP32 state, exact
 // maximum) into device slots, and the next step's first stage turns it into dt (FP64), so
 // a step needs no separate reduction launches; with viscosity the first
-// stage's sensor fills the slots instead (it knows the new viscosity).
+// stage's gradient fills the slots instead (it has the new viscosity).
 #include <hip/hip_runtime.h>
 
 #include <cstring>
