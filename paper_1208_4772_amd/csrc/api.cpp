@@ -621,7 +621,7 @@ int dg_mesh_setup(const dg_mesh_desc *d, void *stream, dg_mesh **out) {
     }
     if (dm.av) {
         // operator fragments of the gradient kernel
-        const size_t nG = grad_opsG_values(P);
+        const size_t nG = grad_opsG_values(P, dm.fp32);
         if (dm.fp32) {
             float *opsG_d;
             if ((rc = m->alloc(&opsG_d, nG))) return cleanup(rc);

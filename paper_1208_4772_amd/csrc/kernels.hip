@@ -381,8 +381,17 @@ struct GradShape {
     static constexpr int Np = (P + 1) * (P + 2) / 2, Nfp = P + 1, NF3 = 3 * Nfp;
     static constexpr int KSD = (Np + 3) / 4, KSL = (NF3 + 3) / 4, MT = (Np + 15) / 16;
     static constexpr int GW = P == 1 ? 2 : 1;                  // column groups per wavefront
-    static constexpr int NT = kBlock / 64 * GW, EB = 4 * NT;   // column groups and elements per block
-    static constexpr int NZ = MT * (2 * KSD + KSL);            // A fragments: Dr, Ds, LIFT
+    // Wavefronts that share a column group's row tiles: in FP64 at P = 5 (two
+    // tiles) both take one, so a block holds 8 elements instead of 16 and each
+    // of its lanes one face node instead of two, whose far-field states (two
+    // powers each) followed one another.  Viscous airfoil, ten steps, one
+    // wavefront / two: 500 elements 1,468 / 1,286 us, 1,500 1,367 / 1,267,
+    // 6,000 1,697 / 1,600, 60,000 6,682 / 6,577 (a kernel on the VALUs: 1,292,
+    // 1,339, 1,732 and 7,464).  In FP32 the sharing costs 1% from 60,000 on.
+    static constexpr int WG = sizeof(T) == 8 ? MT : 1;
+    static constexpr int MW = MT / WG;                         // row tiles of a wavefront
+    static constexpr int NT = kBlock / 64 * GW / WG, EB = 4 * NT;   // column groups and elements per block
+    static constexpr int NZ = MW * (2 * KSD + KSL);            // A fragments of a wavefront: Dr, Ds, LIFT
     static constexpr int NG = (NZ + 3) / 4;
     static constexpr int SJ = 4 * KSL + 1;                     // LDS stride of a column's jumps
     // LDS stride of a node's result: whole 16-byte vectors, spread over the banks
@@ -424,7 +433,7 @@ __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) 
     using S = GradShape<T, P>;
     using V4 = typename Vec<T>::V4;
     using V16 = typename Vec<T>::V16;
-    constexpr int Np = S::Np, Nfp = S::Nfp, NF3 = S::NF3, KSD = S::KSD, KSL = S::KSL, MT = S::MT, GW = S::GW;
+    constexpr int Np = S::Np, Nfp = S::Nfp, NF3 = S::NF3, KSD = S::KSD, KSL = S::KSL, MW = S::MW, WG = S::WG, GW = S::GW;
     constexpr int EB = S::EB, NG = S::NG, SJ = S::SJ, SQ = S::SQ, RG = S::RG, TPT = S::TPT, VW = S::VW, NV = S::NV;
     __shared__ __attribute__((aligned(16))) T sU[EB * kFields * Np];
     __shared__ __attribute__((aligned(16))) T sW[S::NT * RG];
@@ -539,7 +548,7 @@ __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) 
     }
     V4 ga[NG];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) ga[g] = reinterpret_cast<const V4 *>(a.opsG)[g * 64 + lane];
+    for (int g = 0; g < NG; ++g) ga[g] = reinterpret_cast<const V4 *>(a.opsG)[(wave % WG * NG + g) * 64 + lane];
     if constexpr (CFL) {
         double best = 0.0;
         int bad = 0;
@@ -582,39 +591,45 @@ __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) 
     const unsigned col = lane & 15, kq = lane >> 4;
 #pragma unroll
     for (int gi = 0; gi < GW; ++gi) {
-        const unsigned t = wave * GW + gi;
-        if (4 * t >= nel) break;
+        const unsigned t = wave / WG * GW + gi, mt0 = wave % WG * MW;
         const V4 zero = {T(0), T(0), T(0), T(0)};
-        V4 ar[MT], as[MT], ax[MT], ay[MT];
-        // a column's operand rows beyond its length are zero (the columns of
-        // elements past the mesh's end are never written out)
-        const T *ub = sU + (t * 16 + col) * Np, *jx = sW + t * RG + col * 2 * SJ, *jy = jx + SJ;
+        V4 ar[MW], as[MW], ax[MW], ay[MW];
+        if (WG == 1 && 4 * t >= nel) break;   // (of the wavefronts that share a group, none skips the barrier)
+        if (WG == 1 || 4 * t < nel) {
+            // a column's operand rows beyond its length are zero (the columns of
+            // elements past the mesh's end are never written out)
+            const T *ub = sU + (t * 16 + col) * Np, *jx = sW + t * RG + col * 2 * SJ, *jy = jx + SJ;
 #pragma unroll
-        for (int ks = 0; ks < KSD; ++ks) {
-            const unsigned row = 4 * ks + kq;
-            const T b = 4 * ks + 3 < Np || row < Np ? ub[row] : T(0);
+            for (int ks = 0; ks < KSD; ++ks) {
+                const unsigned row = 4 * ks + kq;
+                const T b = 4 * ks + 3 < Np || row < Np ? ub[row] : T(0);
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const int z = ks * MT + mt, y = KSD * MT + z;
-                ar[mt] = mfma16(ga[z / 4][z % 4], b, ks ? ar[mt] : zero);
-                as[mt] = mfma16(ga[y / 4][y % 4], b, ks ? as[mt] : zero);
+                for (int mt = 0; mt < MW; ++mt) {
+                    const int z = ks * MW + mt, y = KSD * MW + z;
+                    ar[mt] = mfma16(ga[z / 4][z % 4], b, ks ? ar[mt] : zero);
+                    as[mt] = mfma16(ga[y / 4][y % 4], b, ks ? as[mt] : zero);
+                }
+            }
+#pragma unroll
+            for (int ks = 0; ks < KSL; ++ks) {
+                const unsigned row = 4 * ks + kq;
+                const bool in = 4 * ks + 3 < NF3 || row < NF3;
+                const T bx = in ? jx[row] : T(0), by = in ? jy[row] : T(0);
+#pragma unroll
+                for (int mt = 0; mt < MW; ++mt) {
+                    const int z = 2 * KSD * MW + ks * MW + mt;
+                    ax[mt] = mfma16(ga[z / 4][z % 4], bx, ks ? ax[mt] : zero);
+                    ay[mt] = mfma16(ga[z / 4][z % 4], by, ks ? ay[mt] : zero);
+                }
             }
         }
-#pragma unroll
-        for (int ks = 0; ks < KSL; ++ks) {
-            const unsigned row = 4 * ks + kq;
-            const bool in = 4 * ks + 3 < NF3 || row < NF3;
-            const T bx = in ? jx[row] : T(0), by = in ? jy[row] : T(0);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const int z = 2 * KSD * MT + ks * MT + mt;
-                ax[mt] = mfma16(ga[z / 4][z % 4], bx, ks ? ax[mt] : zero);
-                ay[mt] = mfma16(ga[z / 4][z % 4], by, ks ? ay[mt] : zero);
-            }
+        // the result over the group's (consumed) jumps
+        if constexpr (WG > 1) {
+            __syncthreads();
+        } else {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
         }
-        // the result over the group's own (consumed) jumps
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
         const unsigned el = t * 4 + (col >> 2), c = col & 3;
         if (el < nel) {
             const T sig = sSig[el];
@@ -622,12 +637,12 @@ __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) 
             T rx = sG[el][0], sx = sG[el][1], ry = sG[el][2], sy = sG[el][3];
             T *ob = sW + t * RG + (el & 3) * (Np * SQ) + c;
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
+            for (int mt = 0; mt < MW; ++mt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     // output row of accumulator slot r (consecutive rows per
                     // 16-lane group in FP32, interleaved by 4 in FP64)
-                    const unsigned i = sizeof(T) == 4 ? 16 * mt + 4 * kq + r : 16 * mt + kq + 4 * r;
+                    const unsigned i = 16 * (mt0 + mt) + (sizeof(T) == 4 ? 4 * kq + r : kq + 4 * r);
                     if (i < Np) {
                         if (curved) {
                             const T *gk = a.geo + (k0 + el) * 4 * Np + i;
@@ -1249,22 +1264,34 @@ void av_fill_args(const DevMesh &m, const void *U, void *eps, void *Q, unsigned 
 
 int sensor_elem_blocks(const DevMesh &m) { return (m.K + kBlock - 1) / kBlock; }
 
-int grad_tiles(const DevMesh &m) {
-    int eb = 16;   // elements per block
-    (void)with_order(m.P, [&](auto PC) {
-        eb = GradShape<float, decltype(PC)::value>::EB;   // the same in both precisions
+template <typename T>
+static int grad_block(int P) {   // elements per block
+    int eb = 16;
+    (void)with_order(P, [&](auto PC) {
+        eb = GradShape<T, decltype(PC)::value>::EB;
         return hipSuccess;
     });
+    return eb;
+}
+
+int grad_tiles(const DevMesh &m) {
+    const int eb = m.fp32 ? grad_block<float>(m.P) : grad_block<double>(m.P);
     return (m.K + eb - 1) / eb;
 }
 
-// Fragments of the gradient's products (Dr, Ds, LIFT): lane l of fragment
-// z = ks MT + mt of an operator holds row 16 mt + l % 16, column 4 ks + l / 16
-// (zero outside the matrix), four fragments per group.
-size_t grad_opsG_values(int P) {
+// Fragments of the gradient's products (Dr, Ds, LIFT), for the row tiles of
+// each of the wavefronts that share a group: lane l of fragment z = ks MW + mt
+// of an operator holds row 16 mt + l % 16, column 4 ks + l / 16 (zero outside
+// the matrix), four fragments per group.
+size_t grad_opsG_values(int P, bool fp32) {
     size_t n = 0;
+    auto values = [&](auto shape) { n = size_t(decltype(shape)::WG) * decltype(shape)::NG * 64 * 4; };
     (void)with_order(P, [&](auto PC) {
-        n = size_t(GradShape<float, decltype(PC)::value>::NG) * 64 * 4;
+        constexpr int PP = decltype(PC)::value;
+        if (fp32)
+            values(GradShape<float, PP>());
+        else
+            values(GradShape<double, PP>());
         return hipSuccess;
     });
     return n;
@@ -1274,18 +1301,20 @@ template <typename T>
 static void fill_opsG(int P, const double *Dr, const double *Ds, const double *LIFT, T *out) {
     (void)with_order(P, [&](auto PC) {
         using S = GradShape<T, decltype(PC)::value>;
-        for (int z = 0; z < S::NG * 64 * 4; ++z) out[z] = T(0);
+        for (int z = 0; z < S::WG * S::NG * 64 * 4; ++z) out[z] = T(0);
         const double *ops[3] = {Dr, Ds, LIFT};
-        int first = 0;
-        for (int o = 0; o < 3; ++o) {
-            const int cols = o < 2 ? S::Np : S::NF3, ksn = (cols + 3) / 4;
-            for (int z = 0; z < ksn * S::MT; ++z)
-                for (int l = 0; l < 64; ++l) {
-                    const int row = 16 * (z % S::MT) + (l & 15), c = 4 * (z / S::MT) + (l >> 4);
-                    if (row < S::Np && c < cols)
-                        out[(((first + z) / 4) * 64 + l) * 4 + (first + z) % 4] = T(ops[o][row * cols + c]);
-                }
-            first += ksn * S::MT;
+        for (int w = 0; w < S::WG; ++w) {
+            int first = 0;
+            for (int o = 0; o < 3; ++o) {
+                const int cols = o < 2 ? S::Np : S::NF3, nz = (cols + 3) / 4 * S::MW;
+                for (int z = 0; z < nz; ++z)
+                    for (int l = 0; l < 64; ++l) {
+                        const int row = 16 * (w * S::MW + z % S::MW) + (l & 15), c = 4 * (z / S::MW) + (l >> 4);
+                        if (row < S::Np && c < cols)
+                            out[((w * S::NG + (first + z) / 4) * 64 + l) * 4 + (first + z) % 4] = T(ops[o][row * cols + c]);
+                    }
+                first += nz;
+            }
         }
         return hipSuccess;
     });

@@ -200,7 +200,7 @@ hipError_t launch_av_batch(int P, bool cfl, const void *jobs, const void *eitems
 int sensor_elem_blocks(const DevMesh &m);
 int grad_tiles(const DevMesh &m);
 // matrix-core fragments of the gradient's operators
-size_t grad_opsG_values(int P);
+size_t grad_opsG_values(int P, bool fp32);
 void grad_fill_opsG(int P, const double *Dr, const double *Ds, const double *LIFT, float *out);
 void grad_fill_opsG64(int P, const double *Dr, const double *Ds, const double *LIFT, double *out);
 // CFL reduction -> scal[S_DT] (dt_fixed > 0 overrides), accumulates S_T,
