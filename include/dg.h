@@ -211,13 +211,15 @@ int dg_step_static(dg_mesh *mesh, void *U, double dt, void *stream);
 
 /* nsteps CFL steps of U in place, then totals and residual; synchronises
  * and fills *stats (may be NULL).  Returns DG_ENONFINITE if the state
- * became non-finite, rho <= 0 or p <= 0 at any step.  FP32 handles take
- * the CFL bound from the stage kernels themselves (without viscosity: the
- * last stage, for the next step, and a kernel with the same per-node
- * arithmetic before the first step; with viscosity: the first stage's
- * sensor), evaluated in FP64 per node from the FP32 state; FP64 handles
- * and dg_step use the FP64 reduction.  Calls compose: dg_run of N steps
- * twice gives the same bits as one dg_run of 2N steps. */
+ * became non-finite, rho <= 0 or p <= 0 at any step, the state the last step
+ * leaves included (nsteps = 0 checks nothing).  The CFL bound is evaluated in
+ * FP64 per face node from the state.  Without viscosity a run's step takes it
+ * from the last stage of the step before (FP32 and weak-form handles, FP64
+ * handles on the matrix cores), the first from a kernel of the same
+ * arithmetic; FP32 handles with viscosity take it from the step's first
+ * gradient; the other FP64 handles, and dg_step, from a reduction per step.
+ * Calls compose: dg_run of N steps twice gives the same bits as one dg_run of
+ * 2N steps. */
 int dg_run(dg_mesh *mesh, void *U, void *work, int nsteps, dg_run_stats *stats, void *stream);
 
 /* Conserved totals sum_k sum_i w_ki U_ki, w_ki = sum_j M_ij J_kj, in FP64
@@ -355,8 +357,9 @@ int dg_batch_advance(dg_batch *batch, int max_steps, void *stream, int *steps_ru
 /* Synchronise the stream and list slots that are done and not yet released
  * (up to max_done ids; *ndone = how many).  A slot is done when it has run
  * all its steps, or when its state check has failed (non-finite state,
- * rho <= 0 or p <= 0): such a slot retires at this poll, and its stats
- * report DG_ENONFINITE and the steps it ran. */
+ * rho <= 0 or p <= 0): such a slot retires at this poll.  The stats of a slot
+ * whose state went bad, that of its last step included, report DG_ENONFINITE
+ * and the steps it ran. */
 int dg_batch_poll(dg_batch *batch, void *stream, int *done_slots, int max_done, int *ndone);
 
 /* Steps done, simulated time, dt range and status of a slot (synchronises). */

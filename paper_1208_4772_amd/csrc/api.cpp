@@ -925,10 +925,10 @@ int dg_run(dg_mesh *m, void *U, void *work, int nsteps, dg_run_stats *stats, voi
     HIP_TRY(launch_reset_scalars(m->dm, st));
     HIP_TRY(hipMemsetAsync(m->dm.flag, 0, sizeof(int), st));
     HIP_TRY(hipEventRecord(e0, st));
-    // fused runs: the bound of each step's state comes from the previous
-    // step's last stage (FP32 matrix-core handles; FP64 handles on the FP64
-    // matrix cores without viscosity; weak-form handles, whose last step
-    // leaves no bound: their final state is not checked)
+    // fused runs: the bound of each step's state, and its check, come from the
+    // previous step's last stage (FP32 matrix-core handles; FP64 handles on
+    // the FP64 matrix cores without viscosity; weak-form handles, whose last
+    // step leaves no bound) or, with viscosity, from its first gradient
     const bool weak = m->dm.weak;
     const bool fused64 = !m->dm.fp32 && m->dm.opsA64 && !m->dm.av;
     const bool fused = weak ? nsteps > 1 : (m->dm.fp32 || fused64);
@@ -951,13 +951,12 @@ int dg_run(dg_mesh *m, void *U, void *work, int nsteps, dg_run_stats *stats, voi
         }
     }
     HIP_TRY(hipEventRecord(e1, st));
-    // a fused viscous run checks each step's state in its first gradient: the
-    // final state still needs the check
-    if (fused && m->dm.av && nsteps > 0) HIP_TRY(launch_cfl_vmax(m->dm, U, m->dm.vmax, st));
-    // diagnostics at the end: totals and the residual ||rhs(U)||_inf
+    // diagnostics at the end: totals, with the check of the final state where
+    // no stage has checked it, and the residual ||rhs(U)||_inf
     char *w = static_cast<char *>(work);
     void *scratch = w + m->off_A();
-    HIP_TRY(launch_totals(m->dm, U, st));
+    const bool checked = fused && !weak && !m->dm.av;
+    HIP_TRY(launch_totals(m->dm, U, nsteps > 0 && !checked, st));
     if (m->dm.av) {
         if (int rc = av_prepare(m, U, w, st)) return rc;
     }
@@ -997,7 +996,7 @@ int dg_totals(dg_mesh *m, const void *U, double out[4], void *stream) {
     if (int rc = check_ptr(U, "U")) return rc;
     if (!out) return fail(DG_EINVAL, "out is NULL");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    HIP_TRY(launch_totals(m->dm, U, st));
+    HIP_TRY(launch_totals(m->dm, U, false, st));
     HIP_TRY(hipMemcpyAsync(out, m->dm.scal + S_TOT, sizeof(double) * 4, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     return DG_OK;
@@ -1704,10 +1703,9 @@ int dg_batch_advance(dg_batch *b, int max_steps, void *stream, int *steps_run) {
             if (s.remaining == 0) {
                 s.finished = true;
                 b->dirty = true;
-                // a batched viscous slot checks each step's state in that
-                // step's first gradient: check the final state as dg_run does
-                if (batched_path(s.mesh) && s.mesh->dm.av)
-                    HIP_TRY(launch_cfl_vmax(s.mesh->dm, s.U, s.mesh->dm.vmax, st));
+                // the final state's check as in dg_run: a batched inviscid
+                // slot's last stage has made it
+                if (!batched_path(s.mesh) || s.mesh->dm.av) HIP_TRY(launch_totals(s.mesh->dm, s.U, true, st));
             }
         }
     for (Slot &s : b->slots)

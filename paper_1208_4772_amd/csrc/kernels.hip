@@ -988,10 +988,12 @@ __global__ __launch_bounds__(kBlock) void k_cfl_finish_vmax(int n, const double 
         slot[threadIdx.x] = threadIdx.x == 0 ? (unsigned long long)__double_as_longlong(vmax) : 0ull;
 }
 
+// Totals of a state; with a flag also its check.
 template <typename T, int P>
 __global__ __launch_bounds__(kBlock) void k_totals(int K, const T *__restrict__ U,
                                                    const double *__restrict__ wmass,
-                                                   double *__restrict__ partial) {
+                                                   double *__restrict__ partial, double g,
+                                                   int *__restrict__ flag) {
     using O = Order<P>;
     constexpr int Np = O::Np;
     __shared__ double sh[kBlock];
@@ -999,8 +1001,12 @@ __global__ __launch_bounds__(kBlock) void k_totals(int K, const T *__restrict__ 
     double v[kFields] = {0, 0, 0, 0};
     if (t.act) {
         const double w = wmass[t.k * Np + t.i];
+        double u[kFields];
 #pragma unroll
-        for (int c = 0; c < kFields; ++c) v[c] = w * double(U[(t.k * kFields + c) * Np + t.i]);
+        for (int c = 0; c < kFields; ++c) u[c] = double(U[(t.k * kFields + c) * Np + t.i]);
+        if (flag && bad_state(g, u)) atomicOr(flag, 1);
+#pragma unroll
+        for (int c = 0; c < kFields; ++c) v[c] = w * u[c];
     }
 #pragma unroll
     for (int c = 0; c < kFields; ++c) {
@@ -1419,11 +1425,11 @@ hipError_t launch_cfl(const DevMesh &m, const void *U, const void *eps, double d
 }
 
 template <typename T>
-static hipError_t totals_t(const DevMesh &m, const void *U, hipStream_t st) {
+static hipError_t totals_t(const DevMesh &m, const void *U, bool check, hipStream_t st) {
     hipError_t e = with_order(m.P, [&](auto PC) {
         constexpr int P = decltype(PC)::value;
         hipLaunchKernelGGL((k_totals<T, P>), dim3(nblocks<P>(m.K)), dim3(kBlock), 0, st, m.K,
-                           static_cast<const T *>(U), m.wmass, m.partial);
+                           static_cast<const T *>(U), m.wmass, m.partial, m.gamma, check ? m.flag : nullptr);
         return hipGetLastError();
     });
     if (e != hipSuccess) return e;
@@ -1432,8 +1438,8 @@ static hipError_t totals_t(const DevMesh &m, const void *U, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_totals(const DevMesh &m, const void *U, hipStream_t st) {
-    return m.fp32 ? totals_t<float>(m, U, st) : totals_t<double>(m, U, st);
+hipError_t launch_totals(const DevMesh &m, const void *U, bool check, hipStream_t st) {
+    return m.fp32 ? totals_t<float>(m, U, check, st) : totals_t<double>(m, U, check, st);
 }
 
 template <typename T>

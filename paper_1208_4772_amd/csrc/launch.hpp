@@ -207,8 +207,8 @@ void grad_fill_opsG64(int P, const double *Dr, const double *Ds, const double *L
 // S_DTMIN/MAX, S_STEPS; raises *flag on bad states.
 hipError_t launch_cfl(const DevMesh &m, const void *U, const void *eps, double dt_fixed,
                       hipStream_t st);
-// conserved totals -> scal[S_TOT..]
-hipError_t launch_totals(const DevMesh &m, const void *U, hipStream_t st);
+// conserved totals -> scal[S_TOT..]; check: raises *flag on bad states too
+hipError_t launch_totals(const DevMesh &m, const void *U, bool check, hipStream_t st);
 // max |rhs| per field -> scal[S_RES..]
 hipError_t launch_residual(const DevMesh &m, const void *rhs, hipStream_t st);
 // eps (state precision) -> double
