@@ -96,6 +96,9 @@ inline bool use_mfma64(int P, bool av, long K, long curved) {
     if (!av && curved == 0) return true;
     return P >= kMinMatrix64 && K >= (P == 5 ? 6144 : (P == 4 ? 2048 : 0));
 }
+// Whether what a launch reads and writes per element stays in the last-level
+// cache: there tiles go XCD by XCD (xcd_tile), beyond it in block order.
+inline bool in_cache(int K, size_t bytes) { return size_t(K) * bytes <= (size_t(256) << 20); }
 // FP64 stage on the matrix cores (stage64.hip): A operand [LIFT -Dr -Ds] in
 // lane order, and the launch
 size_t mfma64_opsA_values(int P);

@@ -592,11 +592,6 @@ hipError_t launch_stage_mfma64(const DevMesh &m, const void *Uin, void *Uout, vo
     a.geo = m.geo64;
     a.cpre = m.cpre;
     a.Q = static_cast<const f64v16 *>(Q);
-    // XCD-contiguous tiles while a stage's buffers stay in the last-level
-    // cache (20,000 elements at P = 3: 1,374 -> 1,249 us a run of 20 steps);
-    // beyond it consecutive blocks on consecutive tiles stream better
-    // (300,000 at P = 5: 14.5 against 15.1 ms)
-    const bool in_cache = 4 * size_t(m.K) * kFields * m.Np * sizeof(double) <= (size_t(256) << 20);
     a.opsA = reinterpret_cast<const f64x4 *>(m.opsA64);
     a.dt = m.scal + S_DT;
     a.bound = bound && !rhs && m.vmax ? 1 : 0;
@@ -607,7 +602,11 @@ hipError_t launch_stage_mfma64(const DevMesh &m, const void *Uin, void *Uout, vo
         constexpr int P = decltype(PC)::value;
         using S = Tri64<P>;
         const int blocks = (m.K + S::EB - 1) / S::EB;
-        a.chunk = in_cache ? xcd_chunk(blocks) : 0;
+        // XCD-contiguous tiles while a stage's buffers stay in the last-level
+        // cache (20,000 elements at P = 3: 1,374 -> 1,249 us a run of 20 steps);
+        // beyond it consecutive blocks on consecutive tiles stream better
+        // (300,000 at P = 5: 14.5 against 15.1 ms)
+        a.chunk = in_cache(m.K, 4 * kFields * S::Np * sizeof(double)) ? xcd_chunk(blocks) : 0;
         const dim3 grid(xcd_grid(blocks)), block(S::NTH);
         if (m.av) {
             // (curved or not: one variant, the tile's test is cheap)
