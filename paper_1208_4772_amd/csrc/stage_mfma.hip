@@ -90,7 +90,7 @@ struct MfmaArgs {
     const float *__restrict__ geoC;    // [Kc][4 Np + 9 Nfp]
     const float *__restrict__ opsA;    // [MT][KS][64] A operand in lane order
     const float *__restrict__ ops;     // Dr | Ds (row-major) for curved elements
-    const f32x4 *__restrict__ Q;       // [K][Np][2] sigma Q: x, then y parts of the four fields (viscous handles)
+    const f32v16 *__restrict__ Q;      // [K][Np][2] sigma Q: x, then y parts of the four fields (viscous handles)
     double *__restrict__ scal;
     const unsigned long long *__restrict__ vmax_in;
     unsigned long long *__restrict__ vmax_out;
@@ -155,7 +155,7 @@ __device__ __forceinline__ void face_task(const MfmaArgs &a, const long k0, cons
         // (wall_visc_jump), the interior value at the far field (so no
         // contribution there)
         if (code != BC_FARFIELD) {
-            const f32x4 *Qm = a.Q + ((k0 + el) * Np + vm) * 2;
+            const f32v16 *Qm = a.Q + ((k0 + el) * Np + vm) * 2;
             const f32x4 vmv = nx * Qm[0] + ny * Qm[1];
             if (code == BC_INTERIOR) {
                 const f32x4 vpv = nx * qpn[0] + ny * qpn[1];
@@ -258,7 +258,7 @@ __device__ __forceinline__ void stage_tile(const MfmaArgs &a, const int tile) {
         tconn[t] = a.conn[k0 + task / NF3];
     }
     const bool flat_ok = 4 * tid < nflt;
-    const f32x4 u4 = *reinterpret_cast<const f32x4 *>(a.Uin + base + (flat_ok ? 4 * tid : 0));
+    const f32x4 u4 = *reinterpret_cast<const f32v16 *>(a.Uin + base + (flat_ok ? 4 * tid : 0));
     // geometry records, four float4 per element: where a tile holds more
     // elements than a quarter of the threads (P = 1), a thread loads two
     float4 g4[GPT];
@@ -278,13 +278,13 @@ __device__ __forceinline__ void stage_tile(const MfmaArgs &a, const int tile) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) upn[t][c] = src[c * Np];
         if constexpr (AV) {
-            const f32x4 *qn = a.Q + ((long)kn * Np + vp) * 2;
+            const f32v16 *qn = a.Q + ((long)kn * Np + vp) * 2;
             qpn[t][0] = qn[0];
             qpn[t][1] = qn[1];
         }
     }
     f32x4 r4 = {0, 0, 0, 0};
-    if (a.mode && a.stage > 0) r4 = *reinterpret_cast<const f32x4 *>(a.R + base + (flat_ok ? 4 * tid : 0));
+    if (a.mode && a.stage > 0) r4 = *reinterpret_cast<const f32v16 *>(a.R + base + (flat_ok ? 4 * tid : 0));
 
     if (tid < NF3) sFN[tid] = face_node_sel<P>(tid / Nfp, tid % Nfp);
     if constexpr (KP > S::KV) {
@@ -342,7 +342,7 @@ __device__ __forceinline__ void stage_tile(const MfmaArgs &a, const int tile) {
         float G[4] = {u[2], u[1] * vy, u[2] * vy + p, (u[3] + p) * vy};
         if constexpr (AV) {
             // viscous flux sigma Q
-            const f32x4 *Qe = a.Q + ((k0 + eln) * Np + in) * 2;
+            const f32v16 *Qe = a.Q + ((k0 + eln) * Np + in) * 2;
             const f32x4 qx = Qe[0], qy = Qe[1];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -535,15 +535,15 @@ __device__ __forceinline__ void stage_tile(const MfmaArgs &a, const int tile) {
     if (flat_ok) {
         const f32x4 rh = *reinterpret_cast<const f32x4 *>(&res(fe, foff));
         if (a.mode == 0) {
-            *reinterpret_cast<f32x4 *>(a.rhs + base + 4 * tid) = rh;
+            *reinterpret_cast<f32v16 *>(a.rhs + base + 4 * tid) = rh;
         } else {
             const float dt = float(dtd);
             const f32x4 rn = a.stage == 0 ? dt * rh : a.ra * r4 + dt * rh;
             // the stage's input state, still in LDS (kept there rather than in
             // registers through the product)
             const f32x4 un = *reinterpret_cast<const f32x4 *>(&sU[4 * tid]) + a.rb * rn;
-            *reinterpret_cast<f32x4 *>(a.R + base + 4 * tid) = rn;
-            *reinterpret_cast<f32x4 *>(a.Uout + base + 4 * tid) = un;
+            *reinterpret_cast<f32v16 *>(a.R + base + 4 * tid) = rn;
+            *reinterpret_cast<f32v16 *>(a.Uout + base + 4 * tid) = un;
             if (a.cfl_accum) *reinterpret_cast<f32x4 *>(&sU[4 * tid]) = un;
         }
     }
@@ -835,7 +835,7 @@ static MfmaArgs make_args(const DevMesh &m, const void *Uin, void *Uout, void *R
     a.geoC = m.geoC;
     a.opsA = m.bf3 ? reinterpret_cast<const float *>(m.opsB) : m.opsA;
     a.ops = m.ops32;
-    a.Q = static_cast<const f32x4 *>(Q);
+    a.Q = static_cast<const f32v16 *>(Q);
     a.scal = m.scal;
     a.vmax_in = step.vmax_in;
     a.vmax_out = step.vmax_out;
