@@ -86,11 +86,14 @@ struct DevMesh {
 // records would need memory of their own (from P = 3 on they take the place
 // of the node coordinates).  A small mesh's stage time is the latency of one
 // tile, and the padded rows make the matrix cores' chain the longer one at
-// P = 4 and 5 (us a step, VALU / matrix cores: cylinder at P = 5 50 / 60 for
-// 1,500 elements, 83 / 75 for 8,000; viscous airfoil at P = 5 123 / 140 for
-// 1,500, 188 / 184 for 8,000; P = 4 43 / 45 for 1,100, viscous 108 / 105 for
-// 1,500).  Large: 80,000-element cylinder at P = 4, an rhs 56 / 42 us;
-// viscous airfoil, 60,000 at P = 4, 512 / 389 us a step.
+// P = 4 and 5 (us a step, VALU / matrix cores: cylinder at P = 5 55 / 63 for
+// 1,500 elements, 69 / 76 for 6,000, 84 / 78 for 8,000; viscous airfoil at
+// P = 5 124 / 134 for 1,500, 181 / 181 for 8,000; P = 4 50 / 47 for 1,100,
+// viscous 112 / 110 for 1,500, a run; single steps are equal there).  Large:
+// 80,000-element cylinder at P = 4, an rhs 54 / 39 us; viscous airfoil, 60,000
+// at P = 4, 448 / 383 us a step.  At P = 3 the matrix cores lose where their
+// tiles of 16 just exceed the compute units and the VALUs' of 24 do not (a run
+// of ten steps, 4,000 elements 565 / 520 us, 4,400 565 / 619, 6,600 604 / 576).
 constexpr int kMinMatrix64 = 3;
 inline bool use_mfma64(int P, bool av, long K, long curved) {
     if (!av && curved == 0) return true;

@@ -103,6 +103,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves64<P, 
     constexpr int TPT = S::TPT, PPT = S::PPT, NV = S::NV;
     __shared__ __attribute__((aligned(16))) double sB[NT][16][KPP];
     __shared__ __attribute__((aligned(16))) double sU[EB * kFields * Np];
+    // The first loads' pointers are read with the tile count, not after the exit
+    // of the surplus blocks: kernel arguments come from memory, and each round
+    // of reads is a part of a small mesh's launch.
+    asm volatile("" ::"s"(a.Uin), "s"(a.finfo), "s"(a.nbr), "s"(a.rec), "s"(a.opsA));
     const long k0 = (long)xcd_tile(a.chunk) * EB;
     if (k0 >= a.K) return;
     const int nel = (int)min((long)EB, (long)a.K - k0);
@@ -111,7 +115,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves64<P, 
     const int nflt = nel * kFields * Np;
     const int nv = nflt / 2;
     const int ntask = nel * NF3;
-    // whether the tile holds a curved element
+    // ---- loads: the tile, then the neighbour traces of this thread's
+    // face-node tasks (task = element * 3 Nfp + face node; a boundary task
+    // reads its own element and ignores it).  Nothing is stored to LDS before
+    // the last is requested, and no load waits for another but the traces for
+    // the connectivity: tile vectors loaded one after the other, the
+    // neighbour's id after its face code and the curved test first of all were
+    // three to five waits more (us a step, before / after: cylinder of 2,100
+    // at P = 4 45.8 / 43.0, straight 50,000 at P = 5 256 / 243, 999,698 5,599 /
+    // 5,226; ten steps of the viscous airfoil, 30,000 at P = 3, 2,190 / 2,155).
+    const f64v16 *Uv = reinterpret_cast<const f64v16 *>(a.Uin + base);
+    f64x2 uv[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) uv[v] = Uv[min(tid + v * NTH, nv - 1)];
+    int infov[TPT];
+    double upn[TPT][kFields];
+#pragma unroll
+    for (int t = 0; t < TPT; ++t) {
+        const int task = min(tid + t * NTH, ntask - 1);
+        const int e = task / NF3, q = task - e * NF3, f = q / Nfp, j = q - f * Nfp;
+        const long k = k0 + e;
+        infov[t] = a.finfo[k];
+        const long kn = a.nbr[k * 3 + f];   // (k itself at a boundary)
+        const int vp = face_node(P, face_nbr_face(infov[t], f), Nfp - 1 - j);
+#pragma unroll
+        for (int c = 0; c < kFields; ++c) upn[t][c] = a.Uin[(kn * kFields + c) * Np + vp];
+    }
+    // whether the tile holds a curved element (asked once its loads are on
+    // their way: two dependent reads)
     bool curved = false;
     if constexpr (CURV) curved = a.cpre[k0 + nel] != a.cpre[k0];
     // the -Dr and -Ds fragments of a curved tile's four products, staged once
@@ -123,29 +154,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves64<P, 
         for (int v = 0; v < NAV; ++v) av[CURV ? v : 0] = a.opsA[NG * 64 + min(tid + v * NTH, 2 * NG * 64 - 1)];
     }
 
-    // ---- loads: the tile, then the neighbour traces of this thread's
-    // face-node tasks (task = element * 3 Nfp + face node; a boundary task
-    // reads its own element and ignores it)
-    const f64v16 *Uv = reinterpret_cast<const f64v16 *>(a.Uin + base);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
         const int z = tid + v * NTH;
-        if (z < nv) reinterpret_cast<f64x2 *>(sU)[z] = Uv[z];
-    }
-    for (int z = 2 * nv + tid; z < nflt; z += NTH) sU[z] = a.Uin[base + z];
-    int infov[TPT];
-    double upn[TPT][kFields];
-#pragma unroll
-    for (int t = 0; t < TPT; ++t) {
-        const int task = min(tid + t * NTH, ntask - 1);
-        const int e = task / NF3, q = task - e * NF3, f = q / Nfp, j = q - f * Nfp;
-        const long k = k0 + e;
-        infov[t] = a.finfo[k];
-        const bool inner = face_bc(infov[t], f) == BC_INTERIOR;
-        const long kn = inner ? (long)a.nbr[k * 3 + f] : k;
-        const int vp = face_node(P, face_nbr_face(infov[t], f), Nfp - 1 - j);
-#pragma unroll
-        for (int c = 0; c < kFields; ++c) upn[t][c] = a.Uin[(kn * kFields + c) * Np + vp];
+        if (z < nv) reinterpret_cast<f64x2 *>(sU)[z] = uv[v];
     }
     if (CURV && curved) {
 #pragma unroll
