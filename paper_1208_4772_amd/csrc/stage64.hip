@@ -614,11 +614,13 @@ hipError_t launch_stage_mfma64(const DevMesh &m, const void *Uin, void *Uout, vo
         constexpr int P = decltype(PC)::value;
         using S = Tri64<P>;
         const int blocks = (m.K + S::EB - 1) / S::EB;
-        // XCD-contiguous tiles while a stage's buffers stay in the last-level
-        // cache (20,000 elements at P = 3: 1,374 -> 1,249 us a run of 20 steps);
-        // beyond it consecutive blocks on consecutive tiles stream better
-        // (300,000 at P = 5: 14.5 against 15.1 ms)
-        a.chunk = in_cache(m.K, 4 * kFields * S::Np * sizeof(double)) ? xcd_chunk(blocks) : 0;
+        // XCD-contiguous tiles while states, register and geometry records stay
+        // in the last-level cache; beyond it consecutive blocks on consecutive
+        // tiles stream better.  Five steps of a straight mesh, XCD by XCD / in
+        // block order: P = 3, 170,000 elements 1,598 / 1,649 us, 200,000 1,966 /
+        // 1,895; P = 4, 115,000 1,422 / 1,524, 130,000 1,633 / 1,607; P = 2,
+        // 250,000 1,812 / 1,821, 300,000 2,206 / 2,172.
+        a.chunk = in_cache(m.K, 16 * (S::Np + 1) * sizeof(double)) ? xcd_chunk(blocks) : 0;
         const dim3 grid(xcd_grid(blocks)), block(S::NTH);
         if (m.av) {
             // (curved or not: one variant, the tile's test is cheap)
