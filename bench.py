@@ -64,11 +64,12 @@ def log(*a):
 
 
 def kernel_source_hash(precision="fp32", av=False, workload=None):
-    """Hash of the sources of the stage's kernels for this precision (with
-    artificial viscosity the sensor and gradient kernels too; the 3D
-    workload's in their own file)."""
+    """Hash of the sources of the stage's kernels for this precision (FP64:
+    matrix cores and VALUs; with artificial viscosity the sensor and gradient
+    kernels too; the 3D workload's in their own file)."""
     h = hashlib.sha256()
-    files = ("kernels.hip", "common.hpp") if precision == "fp64" else ("stage_mfma.hip", "common.hpp")
+    files = (("stage64.hip", "kernels.hip", "common.hpp") if precision == "fp64" else
+             ("stage_mfma.hip", "common.hpp"))
     if av and precision != "fp64":
         files += ("kernels.hip",)
     if workload == "tet3d":
@@ -79,6 +80,13 @@ def kernel_source_hash(precision="fp32", av=False, workload=None):
     return h.hexdigest()[:16]
 
 
+def curved_elements(case):
+    m = case.mesh
+    if m.node_displacement is not None:
+        return case.K
+    return int((m.bc == 1).any(axis=1).sum()) if m.curve is not None else 0
+
+
 def algorithmic_stage_bytes(case, s):
     """HBM bytes one fused stage launch must move (averaged over the 5 stages):
     state in + out and the Runge-Kutta register R (read in 4 of 5 stages,
@@ -87,14 +95,8 @@ def algorithmic_stage_bytes(case, s):
     curved one) and 12 bytes of connectivity per element."""
     import numpy as np
     K, Np, Nfp = case.K, case.Np, case.P + 1
-    m = case.mesh
-    interior_sides = int((m.bc == 0).sum())
-    if m.node_displacement is not None:
-        curved = K
-    elif m.curve is not None:
-        curved = int((m.bc == 1).any(axis=1).sum())
-    else:
-        curved = 0
+    interior_sides = int((case.mesh.bc == 0).sum())
+    curved = curved_elements(case)
     state = K * 4 * Np * s * (3 + 4 / 5)
     traces = interior_sides * Nfp * 4 * s
     geom = (K - curved) * 13 * s + curved * (4 * Np + 9 * Nfp) * s
@@ -102,32 +104,43 @@ def algorithmic_stage_bytes(case, s):
     total = state + traces + geom + conn
     if case.av:
         # the viscous terms add two launches per stage.  Sensor: density and
-        # the element's viscosity ceiling in, viscosity out (the first stage
-        # of a step also reads the rest of the state and the face Fscale for
-        # the time-step bound).  Gradient: state, viscosity, per-node metrics
-        # and face geometry (4 Np + 9 Nfp values) and 16 bytes of
-        # connectivity in, the neighbours' state traces and viscosity,
-        # sigma grad U (8 Np values) out.  Stage: sigma grad U and the
-        # viscosity in, the neighbours' traces of it (8 values per face
-        # node) and their viscosity.
-        sensor = K * (Np * s + 2 * s) + K * (3 * Np + 3 * Nfp) * s / 5
-        grad = (K * ((4 * Np + 1 + 8 * Np + 4 * Np + 9 * Nfp) * s + 16)
-                + interior_sides * (Nfp * 4 * s + s))
-        stage_av = K * (8 * Np * s + s) + interior_sides * (Nfp * 8 * s + s)
+        # the element's viscosity ceiling in, viscosity out.  Gradient: state,
+        # viscosity, the stage's geometric factors and 16 bytes of
+        # connectivity in, the neighbours' state traces and viscosity, sigma Q
+        # (8 Np values) out; in the first of five stages also the face Fscale
+        # of the FP32 time-step bound.  Stage: sigma Q in, and the neighbours'
+        # traces of it (8 values per face node).
+        sensor = K * (Np * s + 2 * s)
+        grad = (K * ((4 * Np + 1 + 8 * Np) * s + 16) + geom + interior_sides * (Nfp * 4 * s + s)
+                + (K * 3 * Nfp * s / 5 if s == 4 else 0))
+        stage_av = K * 8 * Np * s + interior_sides * Nfp * 8 * s
         total += sensor + grad + stage_av
     return total, dict(curved=curved, interior_sides=interior_sides)
 
 
-def stage_kernel_label(case, precision, waves, form="nodal"):
+def fp64_on_matrix_cores(case):
+    """Whether an FP64 nodal handle's stage runs on the matrix cores (the
+    library's rule: straight inviscid meshes always, others from P = 3 on, at
+    P = 4 and 5 from 2,048 and 6,144 elements)."""
+    if not case.av and curved_elements(case) == 0:
+        return True
+    return case.P >= 3 and case.K >= {3: 0, 4: 2048, 5: 6144}[case.P]
+
+
+def stage_kernel_label(case, precision, waves, form="nodal", matrix64=False):
     """The launch(es) one Runge-Kutta stage consists of: the stage kernel, and
     with artificial viscosity the sensor and gradient launches before it
     (their time is in the per-stage average, so their bytes are in the
     algorithmic figure; a step's first stage runs the gradient that also
-    reduces the time-step bound)."""
+    reduces the time-step bound).  matrix64: the FP64 nodal stage on the
+    matrix cores (fp64_on_matrix_cores) instead of the VALUs."""
     av = "true" if case.av else "false"
     if form == "weak":
-        return f"k_stage_weak<{'double' if precision == 'fp64' else 'float'},{case.P}>"
-    if precision == "fp64":
+        T = "double" if precision == "fp64" else "float"
+        return f"k_stage_weak1<{T}>" if case.P == 1 else f"k_stage_weak<{T},{case.P}>"
+    if precision == "fp64" and matrix64:
+        k = f"k_stage_mfma64<{case.P},{av},{'true' if case.av or curved_elements(case) else 'false'}>"
+    elif precision == "fp64":
         k = f"k_stage<double,{case.P},{av}>"
     else:
         k = (f"k_stage_mfma<{case.P},{'true' if precision == 'bf16x3' else 'false'},"
@@ -464,7 +477,7 @@ def main():
     roofline = dict(bound="hbm", achieved=round(achieved, 1), peak=HBM_PEAK_GBS, unit="GB/s",
                     frac=round(achieved / HBM_PEAK_GBS, 4), traffic=traffic,
                     kernel=stage_kernel_label(case, args.precision, tuned.get(args.precision, (0, 0.0))[0],
-                                              args.form),
+                                              args.form, fp64_on_matrix_cores(case)),
                     avg_launch_us=round(avg_s * 1e6, 3),
                     launches=5 * steps,
                     waves_per_block=tuned.get(args.precision, (0, 0.0))[0] or None,
