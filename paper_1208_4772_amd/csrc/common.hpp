@@ -17,6 +17,31 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef float f32v16 __attribute__((ext_vector_type(4), aligned(4)));
 typedef double f64v16 __attribute__((ext_vector_type(2), aligned(8)));
 
+// Vectors of a precision: V4 a matrix-core accumulator, V16 16 bytes (VW
+// values), U16 the same in a caller's buffer.
+template <typename T>
+struct VecOf;
+template <>
+struct VecOf<float> {
+    typedef f32x4 V4;
+    typedef f32x4 V16;
+    typedef f32v16 U16;
+    static constexpr int VW = 4;
+};
+template <>
+struct VecOf<double> {
+    typedef f64x4 V4;
+    typedef f64x2 V16;
+    typedef f64v16 U16;
+    static constexpr int VW = 2;
+};
+__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f64x4 mfma16(double a, double b, f64x4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
 template <int P>
 struct Order {
     static constexpr int Np = (P + 1) * (P + 2) / 2;

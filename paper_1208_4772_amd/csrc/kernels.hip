@@ -402,25 +402,6 @@ struct GradShape {
     static constexpr int NV = (EB * kFields * Np / VW + kBlock - 1) / kBlock;   // 16-byte vectors per thread
 };
 
-template <typename T>
-struct Vec;
-template <>
-struct Vec<float> {
-    typedef f32x4 V4;
-    typedef f32v16 V16;
-};
-template <>
-struct Vec<double> {
-    typedef f64x4 V4;
-    typedef f64v16 V16;
-};
-__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f64x4 mfma16(double a, double b, f64x4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
 // CFL (a step's first stage): also the time-step bound of the state with its
 // viscosity (FP64 per face node, cfl_bound) into the block's slot and the
 // state check, from the tile in LDS while the operators are on their way.  A
@@ -431,8 +412,8 @@ __device__ __forceinline__ f64x4 mfma16(double a, double b, f64x4 c) {
 template <typename T, int P, bool CFL>
 __device__ __forceinline__ void avgrad_body(const AvArgs<T> &a, const int tile) {
     using S = GradShape<T, P>;
-    using V4 = typename Vec<T>::V4;
-    using V16 = typename Vec<T>::V16;
+    using V4 = typename VecOf<T>::V4;
+    using V16 = typename VecOf<T>::U16;
     constexpr int Np = S::Np, Nfp = S::Nfp, NF3 = S::NF3, KSD = S::KSD, KSL = S::KSL, MW = S::MW, WG = S::WG, GW = S::GW;
     constexpr int EB = S::EB, NG = S::NG, SJ = S::SJ, SQ = S::SQ, RG = S::RG, TPT = S::TPT, VW = S::VW, NV = S::NV;
     __shared__ __attribute__((aligned(16))) T sU[EB * kFields * Np];

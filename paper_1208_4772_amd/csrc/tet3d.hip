@@ -70,33 +70,6 @@ __device__ inline void normal_flux3(T g, const T u[kF3], T nx, T ny, T nz, T fn[
     lam = fabs(vn) + fsqrt(g * p * ir);
 }
 
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef double f64x4_t __attribute__((ext_vector_type(4)));
-typedef double f64x2_t __attribute__((ext_vector_type(2)));
-
-// Vector types of the matrix-core stage per precision: V4, an accumulator
-// (and a group of four A fragments); V16, one 16-byte access (VW values).
-template <typename T>
-struct VT;
-template <>
-struct VT<float> {
-    typedef f32x4_t V4;
-    typedef f32x4_t V16;
-    static constexpr int VW = 4;
-};
-template <>
-struct VT<double> {
-    typedef f64x4_t V4;
-    typedef f64x2_t V16;
-    static constexpr int VW = 2;
-};
-__device__ __forceinline__ f32x4_t mfma16(float a, float b, f32x4_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f64x4_t mfma16(double a, double b, f64x4_t c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
 // Shape of the matrix-core stage, in four passes over one small B buffer:
 // the face terms (LIFT, 4 Nfp rows), then the contravariant fluxes along
 // r, s and t (Dr, Ds, Dt, Np rows each, padded to whole k-steps).  Small
@@ -143,7 +116,7 @@ struct Stage3MArgs {
     const T *__restrict__ geo;
     const int *__restrict__ fmap;
     const int *__restrict__ fmask;
-    const typename VT<T>::V4 *__restrict__ opsA;  // [4][NG][64]: face, then r, s, t fragments (NG = max(NGL, NGD));
+    const typename VecOf<T>::V4 *__restrict__ opsA;  // [4][NG][64]: face, then r, s, t fragments (NG = max(NGL, NGD));
                                                   // lane l of fragment z = ks MT + mt: slot z % 4 of group z / 4
     const double *__restrict__ dt;
     // the last stage of a step: also the time-step bound of the new state
@@ -165,9 +138,9 @@ struct Stage3MArgs {
 template <typename T, int P>
 __device__ __forceinline__ void stage3_mfma_body(const Stage3MArgs<T> &a) {
     using S = TetM<P>;
-    using V4 = typename VT<T>::V4;
-    using V16 = typename VT<T>::V16;
-    constexpr int VW = VT<T>::VW;
+    using V4 = typename VecOf<T>::V4;
+    using V16 = typename VecOf<T>::V16;
+    constexpr int VW = VecOf<T>::VW;
     constexpr bool F32 = sizeof(T) == 4;
     constexpr bool KEEP = F32 || P <= 3;   // fluxes and the Runge-Kutta register ahead of their use
     constexpr int Np = S::Np, NF4 = S::NF4, KSD = S::KSD, KSL = S::KSL, KPP = S::KPP, MT = S::MT;
@@ -660,7 +633,7 @@ static hipError_t stage3_mfma(const Tet3Mesh &m, const void *Uin, void *Uout, vo
     a.geo = static_cast<const T *>(m.fp32 ? static_cast<const void *>(m.geo32) : m.geo64);
     a.fmap = m.fmap;
     a.fmask = m.fmask;
-    a.opsA = reinterpret_cast<const typename VT<T>::V4 *>(m.fp32 ? static_cast<const void *>(m.opsA)
+    a.opsA = reinterpret_cast<const typename VecOf<T>::V4 *>(m.fp32 ? static_cast<const void *>(m.opsA)
                                                                   : static_cast<const void *>(m.opsA64));
     a.dt = m.scal + S_DT;
     a.bound = bound ? 1 : 0;

@@ -169,27 +169,6 @@ __device__ __forceinline__ void quad_transpose(T (&x)[4], bool b0, bool b1) {
     }
 }
 
-template <typename T>
-struct WeakVec;
-template <>
-struct WeakVec<float> {
-    typedef f32x4 V4;
-    typedef f32x4 V;
-    typedef f32v16 VG;
-};
-template <>
-struct WeakVec<double> {
-    typedef f64x4 V4;
-    typedef f64x2 V;
-    typedef f64v16 VG;
-};
-__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f64x4 mfma16(double a, double b, f64x4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
 // Waves per SIMD: FP32 four (100,000 elements at P = 4, two steps, 886 us; 924
 // at five and 1,066 at six, which spill), five at P = 2 (300,000 straight
 // elements, four steps, 1,673 against 1,726 us); FP64 three up to P = 3 (947
@@ -214,9 +193,9 @@ constexpr int weak_blocks(int W) {
 template <typename T, int P, int W, bool BOUND>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(weak_waves<T, P, BOUND>()))) void k_stage_weak(WeakArgs<T> a) {
     using S = WeakM<T, P>;
-    using V4 = typename WeakVec<T>::V4;
-    using V = typename WeakVec<T>::V;
-    using VG = typename WeakVec<T>::VG;
+    using V4 = typename VecOf<T>::V4;
+    using V = typename VecOf<T>::V16;
+    using VG = typename VecOf<T>::U16;
     constexpr int Np = S::Np, Nfp = S::Nfp, NF3 = S::NF3, NQ = S::NQ, NG = S::NG, NFG = S::NFG;
     constexpr int KS1 = S::KS1, MT1 = S::MT1, KSF = S::KSF, MG = S::MG, MT2 = S::MT2, VF = S::VF, NZV = S::NZV;
     constexpr int NV = S::NV, TS = S::TS, NTH = 64 * W;
