@@ -362,6 +362,10 @@ int dg_mesh_setup(const dg_mesh_desc *d, void *stream, dg_mesh **out) {
         }                                                                                   \
     } while (0)
 
+    int dev = 0, ncu = 0;
+    SETUP_TRY(hipGetDevice(&dev));
+    SETUP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    dm.ncu = ncu > 0 ? ncu : 256;
     SETUP_TRY(hipMemcpyAsync(nbr_d, nbr.data(), sizeof(int) * nbr.size(), hipMemcpyHostToDevice, st));
     SETUP_TRY(hipMemcpyAsync(finfo_d, finfo.data(), sizeof(int) * finfo.size(), hipMemcpyHostToDevice, st));
     SETUP_TRY(hipMemcpyAsync(x_d, d->x, sizeof(double) * size_t(K) * Np, hipMemcpyHostToDevice, st));
@@ -499,10 +503,6 @@ int dg_mesh_setup(const dg_mesh_desc *d, void *stream, dg_mesh **out) {
         unsigned long long *vmax_d;
         if ((rc = m->alloc(&vmax_d, 2 * kVmaxSlots))) return cleanup(rc);
         dm.vmax = vmax_d;
-        int dev = 0, ncu = 0;
-        SETUP_TRY(hipGetDevice(&dev));
-        SETUP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-        dm.ncu = ncu > 0 ? ncu : 256;
         // workgroup shape: DG_WAVES_PER_BLOCK if set, else the tuning
         // table's choice for this kind of handle, else the default
         if (const char *e = std::getenv("DG_WAVES_PER_BLOCK")) {

@@ -964,7 +964,8 @@ hipError_t stage_weak_t(const DevMesh &m, const void *Uin, void *Uout, void *R, 
                 constexpr int W = decltype(WC)::value;
                 auto launch = [&](auto BC) {
                     constexpr bool BOUND = decltype(BC)::value;
-                    const int want = 8 * ((a.per + W - 1) / W), most = 256 * weak_blocks<T, P, BOUND>(W);
+                    // (a multiple of 8: every XCD's blocks walk the same step)
+                    const int want = 8 * ((a.per + W - 1) / W), most = max(m.ncu * weak_blocks<T, P, BOUND>(W) / 8 * 8, 8);
                     hipLaunchKernelGGL((k_stage_weak<T, P, W, BOUND>), dim3(unsigned(want < most ? want : most)),
                                        dim3(64 * W), 0, st, a);
                 };
@@ -976,7 +977,7 @@ hipError_t stage_weak_t(const DevMesh &m, const void *Uin, void *Uout, void *R, 
                     launch(std::false_type());
             };
             if constexpr (w8 > w4) {
-                if (a.ngroups > 256 * 4) {
+                if (a.ngroups > m.ncu * 4) {
                     go(std::integral_constant<int, 8>());
                     return hipGetLastError();
                 }
