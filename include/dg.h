@@ -249,7 +249,8 @@ int dg_prolong_operator(int P, int Q, double *I);
 int dg_prolong(const dg_mesh *from, const void *U_from, const dg_mesh *to, void *U_to, void *stream);
 
 /* Replay of captured steps.  With graphs enabled (the default), dg_run on
- * an FP32 handle (with or without artificial viscosity) captures two steps
+ * a nodal FP32 handle (with or without artificial viscosity) or an inviscid
+ * nodal FP64 handle on the matrix cores captures two steps
  * into a hipGraph once per (U, work) pair and replays it, which removes
  * per-launch host overhead; the arithmetic is identical to the eager
  * launches.  Graphs are not used while kernel timing is enabled. */
@@ -315,8 +316,8 @@ int dg_mesh_footprint(const dg_mesh *mesh, size_t *bytes);
  * metric terms).  Curved elements keep per-node (nodal form) or
  * per-cubature-point (weak form) metric terms and, in the weak form, their
  * own inverse mass matrix; the others use five to thirteen numbers.  -1 for
- * FP64 nodal handles, whose stage kernel takes per-node metrics for every
- * element.  Errors: DG_EINVAL. */
+ * FP64 nodal handles, some of whose stage kernels take per-node metrics for
+ * every element.  Errors: DG_EINVAL. */
 int dg_mesh_curved(const dg_mesh *mesh, int *curved);
 
 /* Upper estimate of dg_mesh_footprint for a mesh not yet set up, so that a

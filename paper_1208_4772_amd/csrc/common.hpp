@@ -319,7 +319,7 @@ __device__ inline void wall_visc_jump(const T gm[kFields], T nx, T ny, T d[kFiel
 // Block order of the stage kernels: block b runs on XCD b % 8, and each XCD
 // takes a contiguous run of `chunk` tiles, so that a tile's neighbours are
 // mostly in that XCD's own L2 (the viscous gradient of 120,000 elements at
-// P = 3 reads 29 instead of 67 MB).  chunk comes with the kernel's arguments
+// P = 3 reads 30 instead of 67 MB).  chunk comes with the kernel's arguments
 // (the grid size would be one more dependent load before the first address);
 // 0: tiles in block order.  The grid is a multiple of 8; surplus blocks get a
 // tile past the end.

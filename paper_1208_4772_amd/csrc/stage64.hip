@@ -22,8 +22,8 @@
 // along the walls only; their operator fragments come from LDS and the next
 // product's metric terms are requested before each product (requested from
 // the caches one after the other they were the tile's latency: 60,000 curved
-// elements at P = 3, ten steps, 1.75 ms without, 1.64 with, VALU kernel
-// 1.77).  Viscous handles (AV) subtract sigma Q from the fluxes and add the
+// elements at P = 3, ten steps, 1.75 ms without, 1.64 with; now 1.61, VALU
+// kernel 1.71).  Viscous handles (AV) subtract sigma Q from the fluxes and add the
 // viscous face terms.
 #include <hip/hip_runtime.h>
 
@@ -87,8 +87,10 @@ struct Stage64Args {
 
 // five waves per SIMD (at most 96 registers): 901 us on the 1M-element
 // P = 5 mesh, against 1,003 us at the four the default register budget gives
-// and 1,151 us at six (which spills).  Viscous handles take
-// four (K = 30,000 at P = 3: 2.23 ms a run of ten steps against 2.25 at five),
+// and 1,151 us at six (which spills), all with the tile's loads one after the
+// other (847 us a stage now, the bound of a step's last included).  Viscous
+// handles take four (K = 30,000 at P = 3, with those loads: 2.23 ms a run of
+// ten steps against 2.25 at five; 2.16 now),
 // the curved variant four at P = 5, where five spill.
 template <int P, bool AV, bool CURV>
 constexpr int waves64() {
