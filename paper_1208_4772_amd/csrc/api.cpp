@@ -590,7 +590,8 @@ int dg_mesh_setup(const dg_mesh_desc *d, void *stream, dg_mesh **out) {
                 return cleanup(rc);
             SETUP_TRY(launch_cast(wops_d, o32, wops.size(), st));
             SETUP_TRY(launch_cast(geoA_d, a32, size_t(K) * 5, st));
-            SETUP_TRY(launch_cast(geoF_d, f32, size_t(K) * 3 * NG * 3, st));
+            SETUP_TRY(P == 1 ? launch_cast(geoF_d, f32, size_t(K) * 3 * NG * 3, st)
+                             : launch_weak_face_weights(dm, geoF_d, geoA_d, f32, st));
             SETUP_TRY(launch_cast(geoC_d, c32, nC, st));
             SETUP_TRY(launch_cast(fold_d, m32, nM, st));
             dm.wops32 = o32;

@@ -225,6 +225,8 @@ size_t weak_ops_size(int P);
 hipError_t launch_weak_geometry(const DevMesh &m, const double *x, const double *y, const double *Drg,
                                 const double *Dsg, const double *wg, double *geoA, double *geoF, double *geoC,
                                 double *mass, double *work, hipStream_t st);
+hipError_t launch_weak_face_weights(const DevMesh &m, const double *geoF, const double *geoA, float *out,
+                                    hipStream_t st);
 hipError_t launch_stage_weak(const DevMesh &m, const void *Uin, void *Uout, void *R, void *rhs, int stage,
                              bool bound, hipStream_t st);
 // the stage's operator fragments (host operators as in WeakOps)

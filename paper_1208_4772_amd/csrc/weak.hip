@@ -91,6 +91,13 @@ struct WeakM {
     static constexpr int NZV = (NZ + VF - 1) / VF;
     static constexpr int TS = 16 * Np + 4;           // LDS values of a group's tile
     static constexpr int NV = (16 * Np / VF + 63) / 64;   // 16-byte vectors of a tile per lane
+    // whether the running sums of the tile-by-tile update (PART) wait in LDS:
+    // from P = 4 on their registers spill (20,000 elements on the cylinder,
+    // five steps, FP32: P = 5 895 us in registers, 785 in LDS; P = 4 556, 544)
+    template <bool PART>
+    static constexpr bool lds_sum() {
+        return PART && P >= 4;
+    }
 };
 
 template <typename T>
@@ -109,7 +116,7 @@ struct WeakArgs {
     const T *__restrict__ frag;    // [NZV][64][VF] operator fragments
     const T *__restrict__ wq;      // [NQ] cubature weights
     const T *__restrict__ geoA;    // [K][5] r_x s_x r_y s_y J (straight elements)
-    const T *__restrict__ geoF;    // [K][3][NG][3] n_x n_y w_g sJ
+    const T *__restrict__ geoF;    // [K][3][NG][3] n_x n_y w_g sJ (FP32 from P = 2: of a straight element w_g sJ / J)
     const T *__restrict__ geoC;    // [Kc][NQ][4] w_q J (r_x, s_x, r_y, s_y)
     const T *__restrict__ mfold;   // [Kc][Np][Np] M_k^-1 M_ref (P = 1: M_k^-1)
     const int *__restrict__ widx;  // [K] curved slot or -1
@@ -181,16 +188,30 @@ constexpr int weak_waves() {
 }
 
 // Blocks of W wavefronts a compute unit holds at once (LDS and registers).
-template <typename T, int P, bool BOUND>
+template <typename T, int P, bool PART, bool BOUND>
 constexpr int weak_blocks(int W) {
     using S = WeakM<T, P>;
-    const int lds = (S::NZV * 64 * S::VF + W * 2 * S::TS) * int(sizeof(T));
+    const int lds = (S::NZV * 64 * S::VF + W * 2 * S::TS + (S::template lds_sum<PART>() ? W * S::MT2 * 256 : 0)) * int(sizeof(T));
     const int by_lds = 160 * 1024 / lds, by_regs = 4 * weak_waves<T, P, BOUND>() / W;
     const int n = by_lds < by_regs ? by_lds : by_regs;
     return n < 1 ? 1 : n;
 }
 
-template <typename T, int P, int W, bool BOUND>
+// PART (FP32 meshes with curved elements): the update's sum tile by tile, each
+// tile's own sum (up to P = 3 one for a and one for b) added to the running one.
+// A single sum of all 2 NQ + 3 NG products rounds each at its full size, and
+// with M_ref^-1 in the operator V and S cancel in it: the right-hand side was up
+// to 1.4 times as far from FP64 as by the kernel on the VALUs before, which added
+// the two products of a point first and applied the inverse after the
+// cancellation (relative L2: cylinder, 144 elements at P = 5, 1.59e-5 against
+// 1.10e-5; all curved, 200, 1.16e-4 against 8.3e-5; with PART 1.20e-5 and
+// 8.1e-5; over 120 cases of mesh, order and flux 0.98 of the VALU kernel's in
+// the geometric mean, at most 1.16, on 32 elements).  It costs 0 to 1%, on small
+// meshes at P = 5 4%.  The inverse applied as a product of its own after the sum
+// was 1.07 in the mean with a single sum, and tile by tile 0.99 but up to 1.36
+// (P = 2) and at least 3 to 5% slower from 20,000 elements on.  Straight FP32
+// meshes had the single sum before, too.
+template <typename T, int P, int W, bool PART, bool BOUND>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(weak_waves<T, P, BOUND>()))) void k_stage_weak(WeakArgs<T> a) {
     using S = WeakM<T, P>;
     using V4 = typename VecOf<T>::V4;
@@ -201,6 +222,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(weak_wav
     constexpr int NV = S::NV, TS = S::TS, NTH = 64 * W;
     __shared__ __attribute__((aligned(16))) V sA[NZV * 64];
     __shared__ __attribute__((aligned(16))) T sT[W][2][TS];   // a wavefront's state tile and result tile
+    constexpr bool LSUM = S::template lds_sum<PART>();
+    __shared__ __attribute__((aligned(16))) V4 sSum[LSUM ? W * MT2 * 64 : 1];   // a lane's running sums
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 15, kq = lane >> 4, c = lane & 3, le = col >> 2;
     const bool b0 = lane & 1, b1 = lane & 2;
@@ -274,7 +297,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(weak_wav
 #pragma unroll
         for (int m = 0; m < MT2; ++m) acc[m] = zero;
         // the update divides by J on a straight element (M_k = J M_ref): the
-        // volume weights leave J out and the face weights take 1 / J
+        // volume weights leave J out and the face weights take 1 / J (FP32: in
+        // the table, k_weak_face_weights)
         const T iJ = cs >= 0 ? T(1) : T(1) / ga[4];
         V cur;
         // the fragments in order, a vector of VF at a time (z is a constant
@@ -282,6 +306,29 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(weak_wav
         auto frag = [&](int z) -> T {
             if (z % VF == 0) cur = sA[z / VF * 64 + lane];
             return cur[z % VF];
+        };
+        // a tile's products go on from the running sum, or (PART) from zero and
+        // are added to it
+        V4 *sum = sSum + (LSUM ? wave * MT2 * 64 + lane : 0);
+        auto open_sum = [&](V4(&part)[MT2]) {
+#pragma unroll
+            for (int m = 0; m < MT2; ++m) part[m] = PART ? zero : acc[m];
+        };
+        auto close_sum = [&](const V4(&part)[MT2], bool first, bool last) {
+#pragma unroll
+            for (int m = 0; m < MT2; ++m) {
+                if constexpr (LSUM) {
+                    const V4 v = first ? part[m] : sum[m * 64] + part[m];
+                    if (last) {
+                        acc[m] = v;
+                    } else {
+                        sum[m * 64] = v;
+                        asm volatile("" ::"v"(sum) : "memory");   // not kept in registers
+                    }
+                } else {
+                    acc[m] = PART ? acc[m] + part[m] : part[m];
+                }
+            }
         };
         int z = 0;
         // ---- volume: 16 cubature points at a time
@@ -314,14 +361,26 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(weak_wav
             }
             quad_transpose(fa, b0, b1);
             quad_transpose(fb, b0, b1);
+            constexpr bool TWO = PART && P <= 3;   // the products with a and with b apart
+            V4 part[MT2], pb[TWO ? MT2 : 1];
+            open_sum(part);
+#pragma unroll
+            for (int m = 0; m < (TWO ? MT2 : 1); ++m) pb[m] = zero;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (S::used(mt, r, NQ)) {
 #pragma unroll
-                    for (int m = 0; m < MT2; ++m) acc[m] = mfma16(frag(z++), fa[r], acc[m]);
+                    for (int m = 0; m < MT2; ++m) part[m] = mfma16(frag(z++), fa[r], part[m]);
 #pragma unroll
-                    for (int m = 0; m < MT2; ++m) acc[m] = mfma16(frag(z++), fb[r], acc[m]);
+                    for (int m = 0; m < MT2; ++m) {
+                        V4 &q = TWO ? pb[TWO ? m : 0] : part[m];
+                        q = mfma16(frag(z++), fb[r], q);
+                    }
                 }
+            if constexpr (TWO)
+#pragma unroll
+                for (int m = 0; m < MT2; ++m) part[m] = part[m] + pb[m];
+            close_sum(part, mt == 0, false);
         }
         // ---- faces: 16 Gauss points at a time
 #pragma unroll
@@ -339,7 +398,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(weak_wav
             quad_transpose(up, b0, b1);
             const int fg = min(S::row(mt, kq, c), NFG - 1), f = fg / NG;
             const T *gf = a.geoF + (k * NFG + fg) * 3;
-            const T nx = gf[0], ny = gf[1], ws = gf[2] * iJ;
+            const T nx = gf[0], ny = gf[1], ws = sizeof(T) == 4 ? gf[2] : gf[2] * iJ;
             const int code = face_bc(info, f);
             if (code != BC_INTERIOR) ghost_state(a.g, code, um, nx, ny, a.ff, up);
             T fm[kFields], fp[kFields], lm, lp, star[kFields];
@@ -359,12 +418,15 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(weak_wav
 #pragma unroll
             for (int i = 0; i < kFields; ++i) fs[i] = in ? ws * star[i] : T(0);
             quad_transpose(fs, b0, b1);
+            V4 part[MT2];
+            open_sum(part);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (S::used(mt, r, NFG)) {
 #pragma unroll
-                    for (int m = 0; m < MT2; ++m) acc[m] = mfma16(frag(z++), fs[r], acc[m]);
+                    for (int m = 0; m < MT2; ++m) part[m] = mfma16(frag(z++), fs[r], part[m]);
                 }
+            close_sum(part, false, mt == MG - 1);
         }
         // ---- the result into the group's tile, (element, field, node)
 #pragma unroll
@@ -819,6 +881,17 @@ __global__ void k_weak_fold(int Kc, int Np, const double *__restrict__ minv, con
     out[g] = v;
 }
 
+// The FP32 face table from P = 2 on: a straight element's weights divided by J
+// before the cast.  Divided in the kernel, two roundings of J were common to an
+// element's whole face sum and did not cancel against the volume's.
+__global__ void k_weak_face_weights(long n, int per, const double *__restrict__ geoF, const double *__restrict__ geoA,
+                                    const int *__restrict__ widx, float *__restrict__ out) {
+    const long g = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= n) return;
+    const long k = g / per;
+    out[g] = float(g % 3 == 2 && widx[k] < 0 ? geoF[g] / geoA[k * 5 + 4] : geoF[g]);
+}
+
 template <typename F>
 hipError_t with_order_w(int P, F &&f) {
     switch (P) {
@@ -959,30 +1032,41 @@ hipError_t stage_weak_t(const DevMesh &m, const void *Uin, void *Uout, void *R, 
             // mesh's last block (800 FP32 elements at P = 3, 60 steps, 2,163
             // against 2,374 us; 20,000 at P = 2, 20 steps, 1,047 against 1,106
             // us).
-            constexpr int w4 = 4 * weak_blocks<T, P, false>(4), w8 = 8 * weak_blocks<T, P, false>(8);
-            auto go = [&](auto WC) {
-                constexpr int W = decltype(WC)::value;
-                auto launch = [&](auto BC) {
-                    constexpr bool BOUND = decltype(BC)::value;
-                    // (a multiple of 8: every XCD's blocks walk the same step)
-                    const int want = 8 * ((a.per + W - 1) / W), most = max(m.ncu * weak_blocks<T, P, BOUND>(W) / 8 * 8, 8);
-                    hipLaunchKernelGGL((k_stage_weak<T, P, W, BOUND>), dim3(unsigned(want < most ? want : most)),
-                                       dim3(64 * W), 0, st, a);
+            auto go = [&](auto SC) {
+                constexpr bool PART = decltype(SC)::value;
+                constexpr int w4 = 4 * weak_blocks<T, P, PART, false>(4), w8 = 8 * weak_blocks<T, P, PART, false>(8);
+                auto shape = [&](auto WC) {
+                    constexpr int W = decltype(WC)::value;
+                    auto launch = [&](auto BC) {
+                        constexpr bool BOUND = decltype(BC)::value;
+                        // (a multiple of 8: every XCD's blocks walk the same step)
+                        const int want = 8 * ((a.per + W - 1) / W);
+                        const int most = max(m.ncu * weak_blocks<T, P, PART, BOUND>(W) / 8 * 8, 8);
+                        hipLaunchKernelGGL((k_stage_weak<T, P, W, PART, BOUND>), dim3(unsigned(want < most ? want : most)),
+                                           dim3(64 * W), 0, st, a);
+                    };
+                    // (a variant of its own: the bound's registers would spill
+                    // in the other stages too)
+                    if (a.bound)
+                        launch(std::true_type());
+                    else
+                        launch(std::false_type());
                 };
-                // (a variant of its own: the bound's registers would spill
-                // in the other stages too)
-                if (a.bound)
-                    launch(std::true_type());
-                else
-                    launch(std::false_type());
+                if constexpr (w8 > w4) {
+                    if (a.ngroups > m.ncu * 4) {
+                        shape(std::integral_constant<int, 8>());
+                        return;
+                    }
+                }
+                shape(std::integral_constant<int, 4>());
             };
-            if constexpr (w8 > w4) {
-                if (a.ngroups > m.ncu * 4) {
-                    go(std::integral_constant<int, 8>());
+            if constexpr (sizeof(T) == 4) {
+                if (m.wKc > 0) {
+                    go(std::true_type());
                     return hipGetLastError();
                 }
             }
-            go(std::integral_constant<int, 4>());
+            go(std::false_type());
             return hipGetLastError();
         }
     });
@@ -1033,6 +1117,15 @@ hipError_t launch_weak_geometry(const DevMesh &m, const double *x, const double 
     const long n = (long)m.wKc * m.Np * m.Np;
     hipLaunchKernelGGL(k_weak_fold, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, m.wKc, m.Np, mass,
                        m.ops64 + ops_size(m.Np, m.Nfp), work);
+    return hipGetLastError();
+}
+
+hipError_t launch_weak_face_weights(const DevMesh &m, const double *geoF, const double *geoA, float *out,
+                                    hipStream_t st) {
+    const int per = 9 * ((3 * m.P + 2) / 2);   // values of an element
+    const long n = (long)m.K * per;
+    hipLaunchKernelGGL(k_weak_face_weights, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, n, per, geoF, geoA, m.widx,
+                       out);
     return hipGetLastError();
 }
 
