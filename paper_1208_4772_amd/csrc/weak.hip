@@ -58,7 +58,7 @@ struct WShape {
 // they were 25 to 32 KB of loads per four elements).  A large mesh is bound by
 // issue: an FP32 product takes its SIMD 32 cycles and the VALUs' work (fluxes,
 // transposes) adds to that, so 999,698 straight elements at P = 5 run a stage
-// in 852 us, 48% of it the products and 44% the VALUs (100,000 in 100 us; 132
+// in 843 us, 49% of it the products and 44% the VALUs (100,000 in 100 us; 132
 // with a block barrier between the products and the fluxes in LDS).  A small one is bound
 // by the chain of a group's products: 5,000 elements at P = 4 in FP64 take 15
 // us a stage (22 us with the contractions on the VALUs, one element per
